@@ -12,6 +12,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <map>
 #include <mutex>
 #include <new>
@@ -75,6 +76,7 @@ int coords_per_lane(int d) { return d <= 16 ? 1 : (d <= 32 ? 2 : 4); }
 // A group of problems served by one evaluation launch.
 struct EvalClass {
     int DP, family, grad_mode;
+    int split = 0;        // contraction in two f16 parts
     const int *pids_dev;  // into the handle's class table
     std::vector<int> pids;
     int g0 = 0, n = 0;    // the class's samples: a contiguous range
@@ -206,6 +208,24 @@ static int validate_problem(const chisao_problem *p, int idx) {
     return CHISAO_OK;
 }
 
+// Populations of fewer samples are evaluated in float32 even where their
+// problem qualifies for the two-part contraction (evaluations on caller memory
+// use it at any size).  In a small population a mode may hang on one sample
+// that stops within a few percent of eps_grad, so the set of modes found turns
+// on the last bits of a value; those runs keep the bits they have always had.
+// What it costs: a cycle of the d = 64, K = 128 mixture at N = 2048 takes
+// 5.8 ms in float32 and would take 3.4 in two parts; at N = 4096 it is 6.6
+// against 3.8, at N = 65536 42.1 against 19.1.
+constexpr int kTwoPartMinN = 2049;
+
+// Two-part contraction of a matrix-core mixture: the scales, when it qualifies.
+static int two_part_problem(const chisao_problem &p, float *xs, float *kq) {
+    const int DP = pad_dim(p.d, p.family);
+    *kq = 1.0f;
+    if (p.family >= CHISAO_RASTRIGIN || DP == kAluDP) return 0;
+    return two_part_scales(p.d, DP, p.K, p.mu, p.prec, p.lo, p.hi, xs, kq) ? 1 : 0;
+}
+
 static int validate(const chisao_problem *p, const chisao_config *c, int idx) {
     if (!p || !c) return fail(CHISAO_E_INVAL, "null problem or config");
     int rc = validate_problem(p, idx);
@@ -307,8 +327,15 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         HIP_GO(hipMemsetAsync(bad, 0, sizeof(int), st));
         // ---- per-problem constants ----
         // Samples are laid out problem after problem, ordered by (padded d,
-        // family, gradient mode), so the problems of each launch class own a
-        // contiguous range of samples.
+        // family, gradient mode, contraction), so the problems of each launch
+        // class own a contiguous range of samples.
+        std::vector<std::array<float, 64>> xs(P);
+        std::vector<float> kq(P, 1.0f);
+        std::vector<int> two_part(P), split(P);
+        for (int p = 0; p < n_problems; ++p) {
+            two_part[p] = two_part_problem(ps[p], xs[p].data(), &kq[p]);
+            split[p] = two_part[p] && cs[p].N >= kTwoPartMinN;
+        }
         std::vector<int> order(P);
         for (int p = 0; p < n_problems; ++p) order[p] = p;
         // Within a class the problems go in decreasing order of K (a tile's
@@ -316,7 +343,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         // out first and the short ones fill in behind them.
         auto key = [&](int p) {
             const int K = ps[p].family >= CHISAO_RASTRIGIN ? 0 : ps[p].K;
-            return std::make_tuple(pad_dim(ps[p].d, ps[p].family), ps[p].family, cs[p].grad_mode, -K);
+            return std::make_tuple(pad_dim(ps[p].d, ps[p].family), ps[p].family, cs[p].grad_mode, split[p], -K);
         };
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key(a) < key(b); });
         std::vector<int> s0_of(P);
@@ -338,6 +365,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             ProblemDesc &q = h->pdh[p];
             memset(&q, 0, sizeof q);
             float *Pfrag = nullptr, *muB = nullptr, *logc2 = nullptr, *lo, *hi;
+            float *Pfrag2 = nullptr, *muB2 = nullptr, *xs_dev = nullptr;
             ALLOC(lo, float, d);
             ALLOC(hi, float, d);
             HIP_GO(hipMemcpyAsync(lo, pr.lo, sizeof(float) * d, hipMemcpyHostToDevice, st));
@@ -345,8 +373,11 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             const float nu = pr.family == CHISAO_STUDENT_T ? pr.nu : 1.0f;
             if (!closed) {
                 float *tw, *tmu, *tprec;
-                ALLOC(Pfrag, float, K * DP * DP);
-                ALLOC(muB, float, K * DP);
+                // (the float32 tables only where something reads them)
+                if (!split[p]) {
+                    ALLOC(Pfrag, float, K * DP * DP);
+                    ALLOC(muB, float, K * DP);
+                }
                 ALLOC(logc2, float, K);
                 ALLOC(tw, float, K);
                 ALLOC(tmu, float, K * d);
@@ -354,7 +385,14 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
                 HIP_GO(hipMemcpyAsync(tw, pr.log_w, sizeof(float) * K, hipMemcpyHostToDevice, st));
                 HIP_GO(hipMemcpyAsync(tmu, pr.mu, sizeof(float) * K * d, hipMemcpyHostToDevice, st));
                 HIP_GO(hipMemcpyAsync(tprec, pr.prec, sizeof(float) * K * d * d, hipMemcpyHostToDevice, st));
-                HIP_GO(launch_prepare(pr.family, pr.d, (int)DP, pr.K, nu, tw, tmu, tprec, logc2, Pfrag, muB, bad, st));
+                if (two_part[p]) {
+                    ALLOC(Pfrag2, float, K * DP * DP);
+                    ALLOC(muB2, float, K * DP);
+                    ALLOC(xs_dev, float, DP);
+                    HIP_GO(hipMemcpyAsync(xs_dev, xs[p].data(), sizeof(float) * DP, hipMemcpyHostToDevice, st));
+                }
+                HIP_GO(launch_prepare(pr.family, pr.d, (int)DP, pr.K, nu, tw, tmu, tprec, logc2, Pfrag, muB, xs_dev,
+                                      kq[p], Pfrag2, muB2, bad, st));
             }
             q.d = pr.d;
             q.DP = (int)DP;
@@ -365,6 +403,11 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             q.Pfrag = Pfrag;
             q.muB = muB;
             q.logc2 = logc2;
+            q.Pfrag2 = Pfrag2;
+            q.muB2 = muB2;
+            q.xs = xs_dev;
+            q.split = split[p];
+            q.kq = kq[p];
             q.lo = lo;
             q.hi = hi;
             q.N = c.N;
@@ -413,9 +456,9 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         HIP_GO(hipMemcpyAsync(pid_dev, pid.data(), sizeof(uint16_t) * N, hipMemcpyHostToDevice, st));
         D.pid = pid_dev;
         // ---- launch classes ----
-        std::map<std::tuple<int, int, int>, std::vector<int>> ecl;
+        std::map<std::tuple<int, int, int, int>, std::vector<int>> ecl;
         for (int p = 0; p < n_problems; ++p) {
-            ecl[{h->pdh[p].DP, h->pdh[p].family, h->pdh[p].grad_mode}].push_back(p);
+            ecl[{h->pdh[p].DP, h->pdh[p].family, h->pdh[p].grad_mode, h->pdh[p].split}].push_back(p);
         }
         std::vector<int> table;
         for (int p = 0; p < n_problems; ++p) table.push_back(p);  // pid_seq
@@ -428,7 +471,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         size_t off = P;
         for (auto &kv : ecl) {
             EvalClass c;
-            std::tie(c.DP, c.family, c.grad_mode) = kv.first;
+            std::tie(c.DP, c.family, c.grad_mode, c.split) = kv.first;
             c.pids = kv.second;
             c.pids_dev = tab_dev + off;
             off += kv.second.size();
@@ -445,7 +488,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             // (CHISAO_FLAG_NO_AUTOTUNE keeps every launch at the default grid)
             c.t_grid_cap = (h->flags & CHISAO_FLAG_NO_AUTOTUNE)
                                ? 0
-                               : trial_resident_blocks(c.DP, c.family, c.grad_mode == CHISAO_GRAD_ADJOINT);
+                               : trial_resident_blocks(c.DP, c.family, c.split, c.grad_mode == CHISAO_GRAD_ADJOINT);
             h->eclasses.push_back(c);
         }
         // ---- population state ----
@@ -591,6 +634,7 @@ static EvalArgs base_args(chisao_ctx *h, const EvalClass &c) {
     a.list_id = -1;
     a.trial_next = -1;
     a.nz_kind = -1;
+    a.split = c.split;
     return a;
 }
 
@@ -1228,6 +1272,7 @@ extern "C" int chisao_eval(chisao_handle h, int problem, const float *X_dev, int
     c.DP = q.DP;
     c.family = q.family;
     c.grad_mode = grad_mode;
+    c.split = q.xs != nullptr;
     c.pids = {problem};
     c.pids_dev = h->pid_seq + problem;
     HIP_TRY(ext_eval_launches(base_args(h, c), q.d, q.DP, q.family, X_dev, B, f_dev, G_dev, grad_mode, h->stream));
@@ -1346,8 +1391,8 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
         used = (used + bytes + 255) & ~(size_t)255;
         return at;
     };
-    const size_t o_pd = take(sizeof(ProblemDesc)), o_cls = take(sizeof(int)), o_ctl = take(sizeof(Ctl));
-    const size_t o_bad = take(sizeof(int)), o_lo = take(4 * d), o_hi = take(4 * d);
+    const size_t o_pd = take(sizeof(ProblemDesc)), o_cls = take(2 * sizeof(int)), o_ctl = take(sizeof(Ctl));
+    const size_t o_bad = o_cls + sizeof(int), o_xs = take(4 * 64), o_lo = take(4 * d), o_hi = take(4 * d);
     size_t o_pf = 0, o_mub = 0, o_lc = 0, o_w = 0, o_mu = 0, o_prec = 0;
     if (!closed) {
         o_pf = take(4 * K * DP * DP);
@@ -1375,8 +1420,16 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     q.family = p->family;
     q.nu = nu;
     q.nu_plus_d = nu + (float)p->d;
-    q.Pfrag = closed ? nullptr : (const float *)(base + o_pf);
-    q.muB = closed ? nullptr : (const float *)(base + o_mub);
+    float xs[64];
+    const bool two_part = two_part_problem(*p, xs, &q.kq);
+    // one set of tables, the one the evaluation reads
+    float *pf = closed ? nullptr : (float *)(base + o_pf), *mub = closed ? nullptr : (float *)(base + o_mub);
+    float *xs_dev = two_part ? (float *)(base + o_xs) : nullptr;
+    q.Pfrag = two_part ? nullptr : pf;
+    q.muB = two_part ? nullptr : mub;
+    q.Pfrag2 = two_part ? pf : nullptr;
+    q.muB2 = two_part ? mub : nullptr;
+    q.xs = xs_dev;
     q.logc2 = closed ? nullptr : (const float *)(base + o_lc);
     q.lo = (const float *)(base + o_lo);
     q.hi = (const float *)(base + o_hi);
@@ -1398,9 +1451,11 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
         HIP_TRY(hipMemcpyAsync(base + o_w, p->log_w, 4 * K, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(base + o_mu, p->mu, 4 * K * d, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(base + o_prec, p->prec, 4 * K * d * d, hipMemcpyHostToDevice, st));
+        if (two_part) HIP_TRY(hipMemcpyAsync(xs_dev, xs, 4 * DP, hipMemcpyHostToDevice, st));
         HIP_TRY(launch_prepare(p->family, p->d, (int)DP, p->K, nu, (const float *)(base + o_w),
                                (const float *)(base + o_mu), (const float *)(base + o_prec), (float *)(base + o_lc),
-                               (float *)(base + o_pf), (float *)(base + o_mub), (int *)(base + o_bad), st));
+                               two_part ? nullptr : pf, two_part ? nullptr : mub, xs_dev, q.kq, two_part ? pf : nullptr,
+                               two_part ? mub : nullptr, (int *)(base + o_bad), st));
     }
     // one synchronization: the host descriptors above stay alive until their
     // copies are done, and a matrix that is not positive definite is reported
@@ -1423,6 +1478,7 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     a.list_id = -1;
     a.trial_next = -1;
     a.nz_kind = -1;
+    a.split = two_part;
     HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, X_dev, B, f_dev, G_dev, grad_mode, st));
     return CHISAO_OK;
 }

@@ -124,6 +124,14 @@ __device__ __forceinline__ float rows4_sum(float v) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// Largest value over the four rows (a NaN counts as smaller than any number).
+__device__ __forceinline__ float rows4_max(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // Two values per lane summed over the four rows at once: on return rows 0
 // and 2 hold the row sum of a, rows 1 and 3 that of b, each added in the
 // order of rows4_sum ((r0 + r1) + (r2 + r3)), so bitwise the same.
@@ -168,6 +176,9 @@ struct ProblemDesc {
                          // at DP = kAluDP the component records [K][alu_record(W)] instead
     const float *muB;    // [K][4][DP/4]  centre coordinates in B-operand lane order (unused at DP = kAluDP)
     const float *logc2;  // [K] log2 of weight times normaliser
+    // the tables of a contraction in two f16 parts (null: the problem stays in
+    // float32): fragments, scaled centres [K][4][DP/4], coordinate scales [DP]
+    const float *Pfrag2, *muB2, *xs;
     const float *lo, *hi;
     int N, s0;
     int m, n_conv, n_anti, n_cloud, M, ls_max, grad_mode;
@@ -178,6 +189,8 @@ struct ProblemDesc {
     int gate_reps;      // noisy evaluations averaged by the quality gate
     int hk0;            // offset of the problem's 2^hash_lb + 1 deduplication bucket offsets in Dev::hoff
     int hash_lb;        // log2 of the deduplication bucket count (a power of two >= N/4)
+    int split;          // the population's evaluations contract in two f16 parts
+    float kq;           // two parts: factor of the quadratic form and of the gradient sums
 };
 
 // ---------------------------------------------------------------------------

@@ -38,6 +38,8 @@ namespace chisao {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int NB = 2;          // 16-point blocks per wave
 constexpr int kTilePts = 32;  // points per wave in the MFMA tiles
@@ -113,6 +115,106 @@ __device__ __forceinline__ void load_frag_buf(__amdgpu_buffer_rsrc_t rs, int vof
 template <int KS, int MB>
 struct CompRegs {
     float pa[KS][MB];
+    float muB[KS];
+    float lc2;
+};
+
+// ---------------------------------------------------------------------------
+// Two-part contraction.  u = P delta with each operand as a sum of two f16
+// values, x = h + l, h = f16(x) and l = f16(x - h) (round to nearest): the
+// three products l_P h_d + h_P l_d + h_P h_d on the f16 matrix core (16 times
+// the rate of the float32 one), summed in float32; at DP = 32 the fourth,
+// l_P l_d, as well.  h and l hold 23 of the 24 significant bits of x, so a term
+// is off by about a rounding of float32, and a sum goes through 3 DP / 32
+// accumulations instead of DP / 4.  Measured against float64 (relative, 2-norm
+// over 4000 points and more, K = 3 to 128, both families): gradients 1.4e-7
+// where the float32 contraction gives 1.7e-7 (d = 64), 1.1e-7 against 1.2e-7
+// (d = 32), 0.93e-7 against 0.95e-7 (d = 20); values alike (6e-8).  Without
+// l_P l_d the d = 20 gradients were at 1.07e-7, and at d = 12 four products
+// gave 9e-8 against 7e-8: so kTwoPartMinD, and DP = 16 stays in float32.
+//
+// What bounds it: the matrix core's rate under load (the products alone ran at
+// 1480 TFLOP/s) plus the vector instructions that split delta (two conversions
+// and two mixed multiply-adds a pair), which the matrix core does not hide.
+// 262144 points of the d = 64, K = 128 mixture, value and gradient: 2216 us in
+// float32, 856 us in two parts; a cycle of its 65536 samples 42.1 -> 19.1 ms.
+//
+
+// f16 has 5 exponent bits, so operands are scaled by powers of two (exact):
+// coordinate j of points and centres by xs_j = 2^(e_j + b), the matrices by
+// 2^(kTwoPartP - e_i - e_j), with 4^e_j about max_k (P_k)_jj, so that scaled
+// diagonals are at most 2^(kTwoPartP + 1) and, the matrices being positive
+// definite, no entry is larger; b puts the largest distance between two points
+// of the box and the centres, in those units, at no more than 2^kTwoPartX.
+// What a part holds is then good to 2^-25 absolutely where its own 11 bits do
+// not reach.  The rule below keeps that harmless: problems whose box spans
+// more than 2^kTwoPartSpan of the narrowest component's standard deviations,
+// or whose diagonals differ by more than 2^kTwoPartRatio, stay in float32.  A
+// point far outside the box carries a power of two of its own (1 for any other
+// point), so nothing overflows that would not in float32.
+// ---------------------------------------------------------------------------
+constexpr int kTwoPartMinD = 17;  // least dimension: stated above
+constexpr int kTwoPartP = 12, kTwoPartX = 13, kTwoPartSpan = 10, kTwoPartRatio = 12, kTwoPartMaxB = 12;
+
+bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, const float *lo, const float *hi,
+                     float *xs, float *kq) {
+    if (d < kTwoPartMinD) return false;
+    int e[64];
+    double span = 0.0;
+    for (int j = 0; j < d; ++j) {
+        double pmax = 0.0, a = lo[j], z = hi[j];
+        for (int k = 0; k < K; ++k) {
+            pmax = fmax(pmax, (double)prec[((size_t)k * d + j) * d + j]);
+            a = fmin(a, (double)mu[(size_t)k * d + j]);
+            z = fmax(z, (double)mu[(size_t)k * d + j]);
+        }
+        if (!(pmax > 0.0)) return false;  // not positive definite: reported by launch_prepare
+        e[j] = (int)lrint(0.5 * log2(pmax));
+        if (e[j] < -40 || e[j] > 40) return false;
+        span = fmax(span, ldexp(z - a, e[j]));
+    }
+    for (int k = 0; k < K; ++k)
+        for (int j = 0; j < d; ++j)
+            if (!(ldexp((double)prec[((size_t)k * d + j) * d + j], -2 * e[j]) >= ldexp(1.0, -kTwoPartRatio)))
+                return false;
+    if (!(span <= ldexp(1.0, kTwoPartSpan))) return false;
+    const int b = span > 0.0 ? (int)fmin((double)kTwoPartMaxB, kTwoPartX - ceil(log2(span))) : kTwoPartMaxB;
+    for (int j = 0; j < DP; ++j) xs[j] = j < d ? (float)ldexp(1.0, e[j] + b) : 1.0f;
+    *kq = (float)ldexp(1.0, -2 * b - kTwoPartP);
+    return true;
+}
+
+// The coordinate a lane of row g holds at position i of its KS = DP / 4: every
+// fourth one in the operand order of the float32 instruction (K = 4), KS in a
+// row for the f16 one (K = 32: a lane's eight operands of step s are positions
+// 8 s .. 8 s + 7).  In either order the accumulators of block mb, with the rows
+// of P permuted alike, are the lane's positions 4 mb .. 4 mb + 3.
+template <bool H16>
+__device__ __forceinline__ constexpr int lane_coord(int KS, int i, int g) {
+    return H16 ? KS * g + i : 4 * i + g;
+}
+
+// Eight values of a lane as two f16 parts.  neg1 is -1 in a scalar register
+// the compiler cannot see through, which makes h - x one v_fma_mix_f32 (with a
+// literal -1 it converts h back and subtracts, one instruction more).
+__device__ __forceinline__ void two_parts(const float *x, float neg1, f16x8 &hi, f16x8 &lo) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const f32x2 v = {x[j], x[j + 1]};
+        const f16x2 h = __builtin_convertvector(v, f16x2);
+        const f32x2 r = {__builtin_fmaf((float)h[0], neg1, v[0]), __builtin_fmaf((float)h[1], neg1, v[1])};
+        const f16x2 l = __builtin_convertvector(r, f16x2);
+        hi[j] = h[0]; hi[j + 1] = h[1];
+        lo[j] = l[0]; lo[j + 1] = l[1];
+    }
+}
+
+// One component's operands of the two-part contraction: fragments of both
+// parts ([part][K step][row block]), centre coordinates, log2 weight.
+template <int DP>
+struct TwoPartRegs {
+    static constexpr int KS = DP / 4, MB = DP / 16, S = DP / 32;
+    f16x8 pa[2][S][MB];
     float muB[KS];
     float lc2;
 };
@@ -286,7 +388,7 @@ constexpr int kHalfTileMax = 128;
 // in wave order, then runs the epilogue.  Line-search launches are small (a
 // few thousand points), so their time is the latency of one tile's pass over
 // all K components; splitting the components cuts that latency.
-template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT = false>
+template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT, bool H16>
 __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2))) void eval_kernel(EvalArgs a) {
     constexpr int KS = DP / 4;
     constexpr int MB = DP / 16;
@@ -702,11 +804,39 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
         } else {
             // ---- operand registers ---------------------------------------------
             float xB[NB][KS];
+            // two-part problems: the point's own power of two, and the factors
+            // of its quadratic form and gradient sums
+            float cn[H16 ? NB : 1], kqn[H16 ? NB : 1], kgn[H16 ? NB : 1];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const float *row = s_pts + (nb * 16 + n) * LD;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) xB[nb][ks] = row[4 * ks + g];
+                for (int ks = 0; ks < KS; ++ks) xB[nb][ks] = row[lane_coord<H16>(KS, ks, g)];
+            }
+            if constexpr (H16) {
+                const gfloat *xs = as_global(pd.xs), *mu0 = as_global(pd.muB2) + g * KS;
+                float far[NB] = {};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const float sc = xs[lane_coord<H16>(KS, ks, g)], c0 = mu0[ks];
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        xB[nb][ks] *= sc;
+                        far[nb] = fmaxf(far[nb], fabsf(xB[nb][ks] - c0));
+                    }
+                }
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    // a point within 2^14 of the first centre lies within 2^14 +
+                    // 2^kTwoPartX of the others: in f16's range as it is
+                    const float fm = rows4_max(far[nb]);
+                    const int ex = fm > 16384.0f ? 140 - (int)(__float_as_uint(fm) >> 23) : 0;
+                    cn[nb] = ldexpf(1.0f, ex);
+                    kqn[nb] = ldexpf(pd.kq, -2 * ex);
+                    kgn[nb] = ldexpf(pd.kq, -ex);
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) xB[nb][ks] *= cn[nb];
+                }
             }
             float mrun[NB], srun[NB];
             float gacc[NB][GRAD ? KS : 1];
@@ -727,20 +857,34 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             // tracks: flat loads would also count against the LDS counter, and
             // the cross-lane reductions of the epilogue would then wait for them.
             const float nu = pd.nu, nupd = pd.nu_plus_d, inv_nu = 1.0f / nu;
-            CompRegs<KS, MB> ra;
+            typedef typename std::conditional<H16, TwoPartRegs<DP>, CompRegs<KS, MB>>::type Regs;
+            Regs ra;
             // Buffer loads: a scalar resource per table and the component's
             // byte offset in a scalar register, each lane's fixed offset in a
             // vector register, so the loop advances one scalar per table
             // instead of per-lane 64-bit addresses.
             const int Kc = pd.K;
-            const __amdgpu_buffer_rsrc_t rs_pf = table_rsrc(pd.Pfrag, (uint32_t)Kc * DP * DP * 4u);
-            const __amdgpu_buffer_rsrc_t rs_mu = table_rsrc(pd.muB, (uint32_t)Kc * DP * 4u);
+            const __amdgpu_buffer_rsrc_t rs_pf = table_rsrc(H16 ? pd.Pfrag2 : pd.Pfrag, (uint32_t)Kc * DP * DP * 4u);
+            const __amdgpu_buffer_rsrc_t rs_mu = table_rsrc(H16 ? pd.muB2 : pd.muB, (uint32_t)Kc * DP * 4u);
             const __amdgpu_buffer_rsrc_t rs_lc = table_rsrc(pd.logc2, (uint32_t)Kc * 4u);
-            const int pf_lane = lane * MB * 4, mu_lane = g * KS * 4;
-            auto load = [&](int k, CompRegs<KS, MB> &r) {
+            const int mu_lane = g * KS * 4;
+            [[maybe_unused]] const int pf_lane = lane * MB * 4;
+            float neg1 = -1.0f;
+            if constexpr (H16) asm("" : "+s"(neg1));
+            auto load = [&](int k, Regs &r) {
                 const int pf_k = k * DP * DP * 4, mu_k = k * DP * 4;
+                if constexpr (H16) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) load_frag_buf<MB>(rs_pf, pf_lane + ks * kWave * MB * 4, pf_k, r.pa[ks]);
+                    for (int i = 0; i < 2 * r.S * MB; ++i) {
+                        const int part = i % 2, blk = i / 2;  // (the parts of a block are used together)
+                        const int off = (part * r.S * MB + blk) * kWave * 16;
+                        r.pa[part][blk / MB][blk % MB] = __builtin_bit_cast(
+                            f16x8, __builtin_amdgcn_raw_buffer_load_b128(rs_pf, lane * 16 + off, pf_k, 0));
+                    }
+                } else {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) load_frag_buf<MB>(rs_pf, pf_lane + ks * kWave * MB * 4, pf_k, r.pa[ks]);
+                }
 #pragma unroll
                 for (int i = 0; i < KS; i += 4) {
                     const f32x4 vb = __builtin_bit_cast(
@@ -758,7 +902,10 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     rows_pair_split(s_own, srun[0], srun[1]);
                 }
             };
-            auto step = [&](const CompRegs<KS, MB> &r, auto nba) {
+            // (two-part problems) the lane's own block's factor of the quadratic form
+            float kq_own = 1.0f;
+            if constexpr (H16) kq_own = (g & 1) ? kqn[1] : kqn[0];
+            auto step = [&](const Regs &r, auto nba) {
                 constexpr int NBA = decltype(nba)::value;
                 f32x4 acc[NB][MB];
 #pragma unroll
@@ -770,6 +917,35 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                 // the same coordinates 4 ks + g, so delta also serves the
                 // quadratic form below
                 float bv[NB][KS];
+                if constexpr (H16) {
+#pragma unroll
+                    for (int s = 0; s < r.S; ++s) {
+                        f16x8 bh[NB], bl[NB];
+#pragma unroll
+                        for (int nb = 0; nb < NBA; ++nb) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j)
+                                bv[nb][8 * s + j] = fmaf(-r.muB[8 * s + j], cn[nb], xB[nb][8 * s + j]);
+                            two_parts(&bv[nb][8 * s], neg1, bh[nb], bl[nb]);
+                        }
+                        // the small products first, while the accumulator is
+                        // small; consecutive instructions go to different
+                        // accumulators
+                        auto product = [&](const f16x8(&pa)[MB], const f16x8(&b)[NB]) {
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                                for (int nb = 0; nb < NBA; ++nb)
+                                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa[mb], b[nb], acc[nb][mb], 0, 0, 0);
+                        };
+                        __builtin_amdgcn_s_setprio(1);
+                        if constexpr (DP == 32) product(r.pa[1][s], bl);
+                        product(r.pa[1][s], bh);
+                        product(r.pa[0][s], bl);
+                        product(r.pa[0][s], bh);
+                        __builtin_amdgcn_s_setprio(0);
+                    }
+                } else {
                 __builtin_amdgcn_s_setprio(1);
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
@@ -783,6 +959,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     }
                 }
                 __builtin_amdgcn_s_setprio(0);
+                }
                 if constexpr (NBA == 2) {
                     // Both blocks' quadratic forms reduced in one exchange;
                     // rows 0 and 2 then carry block 0's log-sum-exp state and
@@ -797,7 +974,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                             q0 = fmaf(bv[0][4 * mb + rr], acc[0][mb][rr], q0);
                             q1 = fmaf(bv[1][4 * mb + rr], acc[1][mb][rr], q1);
                         }
-                    const float q = rows4_sum_pair(q0, q1);
+                    float q = rows4_sum_pair(q0, q1);
+                    if constexpr (H16) q *= kq_own;
                     float l2, w = 1.0f;
                     if constexpr (FAM == 0) {
                         l2 = r.lc2 - q * (0.5f * kLog2e);
@@ -806,14 +984,15 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                         w = nupd * __builtin_amdgcn_rcpf(nu + q);
                     }
                     const bool moved = l2 > m_own + kLseSlack;
-                    const float mnew = moved ? l2 : m_own;
-                    const float sc = __builtin_amdgcn_exp2f(m_own - mnew);
-                    const float pk = __builtin_amdgcn_exp2f(l2 - mnew);
-                    s_own = fmaf(s_own, sc, pk);
-                    m_own = mnew;
-                    if constexpr (GRAD) {
-                        if (__any(moved)) {
-                            // sc is exactly 1 in the block that did not move
+                    // (few components move the reference, so its rescale is a
+                    // rare branch)
+                    if (__any(moved)) {
+                        // sc is exactly 1 in the block that did not move
+                        const float mnew = moved ? l2 : m_own;
+                        const float sc = __builtin_amdgcn_exp2f(m_own - mnew);
+                        s_own *= sc;
+                        m_own = mnew;
+                        if constexpr (GRAD) {
                             float sc0, sc1;
                             rows_pair_split(sc, sc0, sc1);
 #pragma unroll
@@ -823,6 +1002,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                             }
                         }
                     }
+                    const float pk = __builtin_amdgcn_exp2f(l2 - m_own);
+                    s_own += pk;
                     if constexpr (GRAD) {
                         float pw0, pw1;
                         rows_pair_split(pk * w, pw0, pw1);
@@ -844,6 +1025,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) q = fmaf(bv[nb][4 * mb + rr], acc[nb][mb][rr], q);
                     q = rows4_sum(q);
+                    if constexpr (H16) q *= kqn[nb];
                     float l2, w = 1.0f;
                     if constexpr (FAM == 0) {
                         l2 = r.lc2 - q * (0.5f * kLog2e);
@@ -855,16 +1037,18 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     // than 2^kLseSlack: terms stay below 2^kLseSlack, and the
                     // gradient sums are rescaled far less often
                     const bool moved = l2 > mrun[nb] + kLseSlack;
-                    const float mnew = moved ? l2 : mrun[nb];
-                    const float sc = __builtin_amdgcn_exp2f(mrun[nb] - mnew);
-                    const float pk = __builtin_amdgcn_exp2f(l2 - mnew);
-                    srun[nb] = fmaf(srun[nb], sc, pk);
-                    mrun[nb] = mnew;
-                    if constexpr (GRAD) {
-                        if (__any(moved)) {
+                    if (__any(moved)) {
+                        const float mnew = moved ? l2 : mrun[nb];
+                        const float sc = __builtin_amdgcn_exp2f(mrun[nb] - mnew);
+                        srun[nb] *= sc;
+                        mrun[nb] = mnew;
+                        if constexpr (GRAD)
 #pragma unroll
                             for (int i = 0; i < KS; ++i) gacc[nb][i] *= sc;
-                        }
+                    }
+                    const float pk = __builtin_amdgcn_exp2f(l2 - mrun[nb]);
+                    srun[nb] += pk;
+                    if constexpr (GRAD) {
                         const float pw = pk * w;
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb)
@@ -885,7 +1069,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                 // component, which keeps the loop branch-free
                 auto run = [&](auto nba) {
                     if (kb < ke) {
-                        CompRegs<KS, MB> rb;
+                        Regs rb;
                         load(kb, ra);
                         for (int k = kb; k < ke; k += 2) {
                             load(min(k + 1, ke - 1), rb);
@@ -966,9 +1150,12 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                 if constexpr (GRAD) {
                     const float inv = -1.0f / srun[nb];
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) s_g[pt * LD + 4 * (4 * mb + r) + g] = gacc[nb][mb * 4 + r] * inv;
+                    for (int i = 0; i < KS; ++i) {
+                        const int c = lane_coord<H16>(KS, i, g);
+                        float gv = gacc[nb][i] * inv;
+                        if constexpr (H16) gv *= as_global(pd.xs)[c] * kgn[nb];
+                        s_g[pt * LD + c] = gv;
+                    }
                 }
             }
             __syncthreads();
@@ -1072,14 +1259,15 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
 // ---------------------------------------------------------------------------
 // Dispatch
 // ---------------------------------------------------------------------------
-template <int DP, int FAM>
+template <int DP, int FAM, bool H16>
 static hipError_t dispatch_modes(const EvalArgs &a, int center, bool fd, bool grad, dim3 grid, hipStream_t st) {
     const dim3 block(kWave);
-#define CHISAO_GO(C, G, F) hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, 1>), grid, block, 0, st, a)
-#define CHISAO_GO_HALF(G) hipLaunchKernelGGL((eval_kernel<DP, FAM, G, kDirect, false, 1, true>), grid, block, 0, st, a)
-#define CHISAO_GO_SPLIT(C, G, F)                                                                       \
-    hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, trial_split<DP, FAM>()>), grid, dim3(kWave * trial_split<DP, FAM>()), 0, \
-                       st, a)
+    constexpr int S = trial_split<DP, FAM>();
+#define CHISAO_GO(C, G, F) hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, 1, false, H16>), grid, block, 0, st, a)
+#define CHISAO_GO_HALF(G) \
+    hipLaunchKernelGGL((eval_kernel<DP, FAM, G, kDirect, false, 1, true, H16>), grid, block, 0, st, a)
+#define CHISAO_GO_SPLIT(C, G, F) \
+    hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, S, false, H16>), grid, dim3(kWave * S), 0, st, a)
     constexpr bool kHalfOk = FAM < kFamClosed && DP != kAluDP;  // tiles of two MFMA column blocks
     if (center == kDirect) {
         if (fd) CHISAO_GO(kDirect, false, true);
@@ -1106,7 +1294,7 @@ static hipError_t dispatch_modes(const EvalArgs &a, int center, bool fd, bool gr
 // Workgroups of a line-search launch resident at once on the current device
 // (the occupancy of the class's split trial kernel times the CU count), or 0
 // where line-search tiles are not split.
-template <int DP, int FAM>
+template <int DP, int FAM, bool H16>
 static int trial_resident(bool grad) {
     constexpr int S = trial_split<DP, FAM>();
     if constexpr (S == 1) {
@@ -1114,9 +1302,9 @@ static int trial_resident(bool grad) {
     } else {
         int nb = 0, dev = 0, cus = 0;
         const hipError_t e = grad ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                        &nb, eval_kernel<DP, FAM, true, kTrial, false, S>, kWave * S, 0)
+                                        &nb, eval_kernel<DP, FAM, true, kTrial, false, S, false, H16>, kWave * S, 0)
                                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                        &nb, eval_kernel<DP, FAM, false, kTrial, false, S>, kWave * S, 0);
+                                        &nb, eval_kernel<DP, FAM, false, kTrial, false, S, false, H16>, kWave * S, 0);
         if (e != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
             (void)hipGetLastError();  // no limit then; leave no error for later launches to report
@@ -1126,14 +1314,33 @@ static int trial_resident(bool grad) {
     }
 }
 
-int trial_resident_blocks(int DP, int family, bool grad) {
+template <int DP>
+static int trial_resident_dp(int family, bool split, bool grad) {
+    if constexpr (DP >= 32)
+        if (split) return family == 0 ? trial_resident<DP, 0, true>(grad) : trial_resident<DP, 1, true>(grad);
+    return family == 0 ? trial_resident<DP, 0, false>(grad) : trial_resident<DP, 1, false>(grad);
+}
+
+int trial_resident_blocks(int DP, int family, bool split, bool grad) {
     if (family >= kFamClosed) return 0;
     switch (DP) {
-        case 16: return family == 0 ? trial_resident<16, 0>(grad) : trial_resident<16, 1>(grad);
-        case 32: return family == 0 ? trial_resident<32, 0>(grad) : trial_resident<32, 1>(grad);
-        case 64: return family == 0 ? trial_resident<64, 0>(grad) : trial_resident<64, 1>(grad);
+        case 16: return trial_resident_dp<16>(family, split, grad);
+        case 32: return trial_resident_dp<32>(family, split, grad);
+        case 64: return trial_resident_dp<64>(family, split, grad);
         default: return 0;
     }
+}
+
+template <int DP>
+static hipError_t dispatch_family(const EvalArgs &a, int fam, int center, bool fd, bool grad, dim3 grid,
+                                  hipStream_t st) {
+    if constexpr (DP >= 32)
+        if (a.split && fam < kFamClosed)
+            return fam == 0 ? dispatch_modes<DP, 0, true>(a, center, fd, grad, grid, st)
+                            : dispatch_modes<DP, 1, true>(a, center, fd, grad, grid, st);
+    if (fam == 0) return dispatch_modes<DP, 0, false>(a, center, fd, grad, grid, st);
+    if (fam == 1) return dispatch_modes<DP, 1, false>(a, center, fd, grad, grid, st);
+    return dispatch_modes<DP, kFamClosed, false>(a, center, fd, grad, grid, st);
 }
 
 hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool fd, bool grad, hipStream_t st) {
@@ -1148,21 +1355,16 @@ hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool f
     // the closed forms share one instantiation per padded dimension and
     // select the function per problem
     const int fam = family >= kFamClosed ? kFamClosed : family;
-#define CHISAO_FAMS(DPV)                                                                  \
-    fam == 0   ? dispatch_modes<DPV, 0>(a, center, fd, grad, grid, st)                   \
-    : fam == 1 ? dispatch_modes<DPV, 1>(a, center, fd, grad, grid, st)                   \
-               : dispatch_modes<DPV, kFamClosed>(a, center, fd, grad, grid, st)
     switch (DP) {
         case kAluDP:  // mixtures only
-            return fam == 0   ? dispatch_modes<kAluDP, 0>(a, center, fd, grad, grid, st)
-                   : fam == 1 ? dispatch_modes<kAluDP, 1>(a, center, fd, grad, grid, st)
+            return fam == 0   ? dispatch_modes<kAluDP, 0, false>(a, center, fd, grad, grid, st)
+                   : fam == 1 ? dispatch_modes<kAluDP, 1, false>(a, center, fd, grad, grid, st)
                               : hipErrorInvalidValue;
-        case 16: return CHISAO_FAMS(16);
-        case 32: return CHISAO_FAMS(32);
-        case 64: return CHISAO_FAMS(64);
+        case 16: return dispatch_family<16>(a, fam, center, fd, grad, grid, st);
+        case 32: return dispatch_family<32>(a, fam, center, fd, grad, grid, st);
+        case 64: return dispatch_family<64>(a, fam, center, fd, grad, grid, st);
         default: return hipErrorInvalidValue;
     }
-#undef CHISAO_FAMS
 }
 
 // ---------------------------------------------------------------------------
@@ -1171,9 +1373,37 @@ hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool f
 // layouts (or, at the VALU width, the component records).  bad[0] is set when
 // a matrix is not positive definite.
 // ---------------------------------------------------------------------------
+// Two-part tables of component k: fragments [part][K step][row block][lane]
+// in the f16 instruction's A-operand order, rows permuted as lane_coord
+// states, and the scaled centre in the lanes' order ([row][position]).
+__device__ void two_part_tables(int d, int DP, int k, int lane, const float *A, const float *mu, const float *xs,
+                                float kq, float *Pfrag, float *muB) {
+    const int KS = DP / 4, MB = DP / 16, S = DP / 32;
+    _Float16 *P = reinterpret_cast<_Float16 *>(Pfrag + (size_t)k * DP * DP);
+    const int rho = lane & 15;
+    for (int s = 0; s < S; ++s)
+        for (int mb = 0; mb < MB; ++mb)
+            for (int j = 0; j < 8; ++j) {
+                const int row = lane_coord<true>(KS, 4 * mb + (rho & 3), rho >> 2), col = lane_coord<true>(KS, 8 * s + j, lane >> 4);
+                float v = 0.0f;
+                // scaled by 2^(kTwoPartP - e_row - e_col) = 1 / (kq xs_row xs_col)
+                if (row < d && col < d)
+                    v = ldexpf(A[row * d + col], -(ilogbf(kq) + ilogbf(xs[row]) + ilogbf(xs[col])));
+                const _Float16 h = (_Float16)v, l = (_Float16)(v - (float)h);
+                const size_t o = ((size_t)(s * MB + mb) * kWave + lane) * 8 + j;
+                P[o] = h;
+                P[(size_t)S * MB * kWave * 8 + o] = l;
+            }
+    if (lane < DP) {
+        const int c = lane_coord<true>(KS, lane % KS, lane / KS);
+        muB[(size_t)k * DP + lane] = c < d ? mu[c] * xs[c] : 0.0f;
+    }
+}
+
 __global__ __launch_bounds__(64) void prepare_kernel(int family, int d, int DP, int K, float nu, const float *log_w,
                                                      const float *mu, const float *prec, float *logc2, float *Pfrag,
-                                                     float *muB, int *bad) {
+                                                     float *muB, const float *xs, float kq, float *Pfrag2,
+                                                     float *muB2, int *bad) {
     const int k = blockIdx.x;
     const int lane = threadIdx.x;
     __shared__ double L[64 * 64];
@@ -1236,6 +1466,8 @@ __global__ __launch_bounds__(64) void prepare_kernel(int family, int d, int DP, 
         if (lane > 0 && lane < R - T - W) rec[T + W + lane] = 0.0f;
         return;
     }
+    if (xs) two_part_tables(d, DP, k, lane, A, mu + (size_t)k * d, xs, kq, Pfrag2, muB2);
+    if (!Pfrag) return;
     // fragments with permuted rows: Pfrag[k][ks][lane][mb] = P[pi][4 ks + lane/16],
     // pi = 4 (4 mb + rho % 4) + rho / 4 for rho = lane % 16
     const int KS = DP / 4, MB = DP / 16;
@@ -1255,9 +1487,10 @@ __global__ __launch_bounds__(64) void prepare_kernel(int family, int d, int DP, 
 }
 
 hipError_t launch_prepare(int family, int d, int DP, int K, float nu, const float *log_w, const float *mu,
-                          const float *prec, float *logc2, float *Pfrag, float *muB, int *bad, hipStream_t st) {
-    hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(64), 0, st, family, d, DP, K, nu, log_w, mu, prec, logc2,
-                       Pfrag, muB, bad);
+                          const float *prec, float *logc2, float *Pfrag, float *muB, const float *xs, float kq,
+                          float *Pfrag2, float *muB2, int *bad, hipStream_t st) {
+    hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(64), 0, st, family, d, DP, K, nu, log_w, mu, prec, logc2, Pfrag,
+                       muB, xs, kq, Pfrag2, muB2, bad);
     return hipGetLastError();
 }
 

@@ -39,6 +39,7 @@ struct EvalArgs {
     int nz_kind;          // evaluation noise of noisy problems: -1 none, 0 one draw per value, 1 gate mean
     int half_tiles;       // direct value (+ gradient) launches of matrix-core classes: 16-point tiles
     uint32_t nz_base;     // noise sub-stream base (kind 0); the noise step is `step`
+    int split;            // contract in two f16 parts (the problems have those tables)
 };
 
 // center: kDirect / kTrial / kProbe; fd: stencil around each centre;
@@ -49,13 +50,21 @@ hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool f
 // current GPU (0: no limit applies).  Line-search launches use that many
 // workgroups, each looping over tiles: one round of persistent workgroups
 // instead of a queue of one-tile workgroups.
-int trial_resident_blocks(int DP, int family, bool grad);
+int trial_resident_blocks(int DP, int family, bool split, bool grad);
 
 // Per-component constants: log2 normalisers (float64 Cholesky of each
 // precision matrix) and the fragment layouts of the precision matrices and
-// centres.  Writes D.logc2/Pfrag/muB (device buffers passed as mutable).
+// centres (device buffers): in float32 (Pfrag, muB; null: not wanted) and, xs
+// not null, in two f16 parts (Pfrag2, muB2) with the coordinate scales xs
+// (device, [DP]) and their kq.
 hipError_t launch_prepare(int family, int d, int DP, int K, float nu, const float *log_w, const float *mu,
-                          const float *prec, float *logc2, float *Pfrag, float *muB, int *bad, hipStream_t st);
+                          const float *prec, float *logc2, float *Pfrag, float *muB, const float *xs, float kq,
+                          float *Pfrag2, float *muB2, int *bad, hipStream_t st);
+
+// Whether a mixture contracts in two f16 parts, and with which scales
+// (xs [DP], host): the rule and the scales are stated with the definition.
+bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, const float *lo, const float *hi,
+                     float *xs, float *kq);
 
 // Cycle kernels (phases 1-6 and their bookkeeping).
 hipError_t launch_fill_u8(uint8_t *p, uint8_t v, size_t n, hipStream_t st);
