@@ -195,7 +195,8 @@ class Optimizer:
 
     def set_state(self, X=None, stuck=None, active=None, k=None, gr=None, Wd=None, wvalid=None, problem: int = 0):
         sp = self.specs[problem]
-        cur = self.get_state(problem=problem)
+        cur = L.State()  # the generation state alone: no array is asked for
+        L.check(self.lib.chisao_get_state(self.h, problem, C.byref(cur)), "chisao_get_state")
         keep = []
 
         def ptr(a, dt, shape):
@@ -207,9 +208,9 @@ class Optimizer:
 
         gr = gr or {}
         s = L.State(ptr(X, np.float32, (sp.N, sp.d)), None, None, ptr(stuck, np.uint8, (sp.N,)),
-                    ptr(active, np.uint8, (sp.N,)), None, None, None, cur["k"] if k is None else int(k),
-                    gr.get("gr_disabled", cur["gr_disabled"]), gr.get("gr_fail", cur["gr_fail"]),
-                    gr.get("gr_used_last", cur["gr_used_last"]), gr.get("gr_prev_modes", cur["gr_prev_modes"]))
+                    ptr(active, np.uint8, (sp.N,)), None, None, None, cur.k if k is None else int(k),
+                    gr.get("gr_disabled", cur.gr_disabled), gr.get("gr_fail", cur.gr_fail),
+                    gr.get("gr_used_last", cur.gr_used_last), gr.get("gr_prev_modes", cur.gr_prev_modes))
         s.Wd = ptr(Wd, np.float32, (sp.N, sp.d))
         s.wvalid = ptr(wvalid, np.uint8, (sp.N,))
         L.check(self.lib.chisao_set_state(self.h, problem, C.byref(s)), "chisao_set_state")

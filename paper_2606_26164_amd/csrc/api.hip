@@ -108,6 +108,7 @@ struct chisao_ctx {
     std::vector<ProblemDesc> pdh;  // host copy of the descriptors
     std::vector<EvalClass> eclasses;
     const int *pid_seq = nullptr;  // device [P]: 0, 1, ..., P-1
+    int *io_flag = nullptr;        // device: first offending row of a box check
     Buffers buf;
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // [0]: cycles before n_osc, [1]: the last cycle
     // profiling: event pairs recorded around launches of each class
@@ -256,6 +257,18 @@ extern "C" const char *chisao_last_error(void) { return g_err.c_str(); }
 // Creation
 // ---------------------------------------------------------------------------
 static int autotune(chisao_ctx *h);
+
+// The first of a problem's dense device rows with a coordinate outside its box
+// (-1: none); synchronizes.
+static int first_outside(chisao_ctx *h, const float *x_dev, const ProblemDesc &q, bool nan_ok, int *first) {
+    const int none = 0x7FFFFFFF;
+    HIP_TRY(hipMemcpyAsync(h->io_flag, &none, sizeof none, hipMemcpyHostToDevice, h->stream));
+    HIP_TRY(launch_box_check(x_dev, q.d, q.N, q.lo, q.hi, nan_ok, h->io_flag, h->stream));
+    HIP_TRY(hipMemcpyAsync(first, h->io_flag, sizeof *first, hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    if (*first == none) *first = -1;
+    return CHISAO_OK;
+}
 
 extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chisao_problem *ps,
                                    const chisao_config *cs, const float *const *x0_dev, void *hip_stream) {
@@ -529,6 +542,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         ALLOC(D.records, CycleRecord, P * (size_t)D.n_osc);
         ALLOC(D.part, double, P * (size_t)D.n_part_blocks * 129);
         ALLOC(D.prof, unsigned long long, kProfClasses);
+        ALLOC(h->io_flag, int, 1);
         HIP_GO(hipMemsetAsync(D.X, 0, sizeof(float) * N * DSz, st));
         // row arrays start at zero: the L-BFGS kernel reads whole aligned
         // chunks and relies on the columns past each problem's d being zero
@@ -568,14 +582,11 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             for (int p = 0; p < n_problems; ++p) {
                 if (!x0_dev[p]) continue;
                 const ProblemDesc &q = h->pdh[p];
-                std::vector<float> xh((size_t)q.N * q.d);
-                HIP_GO(hipMemcpy(xh.data(), x0_dev[p], sizeof(float) * xh.size(), hipMemcpyDeviceToHost));
-                for (size_t i = 0; i < xh.size(); ++i) {
-                    const size_t j = i % q.d;
-                    if (!(xh[i] >= ps[p].lo[j] && xh[i] <= ps[p].hi[j])) {
-                        rc = fail(CHISAO_E_INVAL, "problem %d: x0 sample %zu lies outside the box", p, i / q.d);
-                        goto fail_out;
-                    }
+                int first = -1;
+                if ((rc = first_outside(h, x0_dev[p], q, false, &first))) goto fail_out;
+                if (first >= 0) {
+                    rc = fail(CHISAO_E_INVAL, "problem %d: x0 sample %d lies outside the box", p, first);
+                    goto fail_out;
                 }
             }
         }
@@ -1088,10 +1099,20 @@ static int check_problem(chisao_ctx *h, int p) {
     return CHISAO_OK;
 }
 
-// rows [s0, s0+N) of a stride-DS device array to a dense host array of stride w
-static hipError_t rows_d2h(void *dst, const void *src, size_t elem, size_t w, size_t DS, size_t s0, size_t N) {
-    return hipMemcpy2D(dst, w * elem, (const char *)src + s0 * DS * elem, DS * elem, w * elem, N,
-                       hipMemcpyDeviceToHost);
+// Rows of problem q in a stride-DS device array to a dense host array and
+// back, through the problem's part of Gh (free between cycles).  Both wait.
+static hipError_t rows_d2h(chisao_ctx *h, float *dst, const float *src, const ProblemDesc &q) {
+    const size_t DS = h->D.DS, at = q.s0 * DS, bytes = sizeof(float) * (size_t)q.N * q.d;
+    if (q.d == h->D.DS) return hipMemcpy(dst, src + at, bytes, hipMemcpyDeviceToHost);
+    hipError_t e = launch_pack_rows(src + at, h->D.DS, q.d, q.N, h->D.Gh + at, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(dst, h->D.Gh + at, bytes, hipMemcpyDeviceToHost, h->stream);
+    return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
+}
+static hipError_t rows_h2d(chisao_ctx *h, float *dst, const float *src, const ProblemDesc &q) {
+    const size_t at = q.s0 * (size_t)h->D.DS;
+    hipError_t e = hipMemcpyAsync(h->D.Gh + at, src, sizeof(float) * (size_t)q.N * q.d, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess) e = launch_unpack_rows(h->D.Gh + at, q.d, h->D.DS, q.N, dst + at, h->stream);
+    return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
 }
 
 extern "C" int chisao_get_state(chisao_handle h, int problem, chisao_state *s) {
@@ -1103,14 +1124,16 @@ extern "C" int chisao_get_state(chisao_handle h, int problem, chisao_state *s) {
     const size_t N = q.N, d = q.d, DS = D.DS, s0 = q.s0, m = q.m, mx = D.mmax;
     HIP_TRY(hipSetDevice(h->device));
     HIP_TRY(hipStreamSynchronize(h->stream));
-    if (s->X) HIP_TRY(rows_d2h(s->X, D.X, 4, d, DS, s0, N));
+    if (s->X) HIP_TRY(rows_d2h(h, s->X, D.X, q));
     if (s->F) HIP_TRY(hipMemcpy(s->F, D.F + s0, sizeof(float) * N, hipMemcpyDeviceToHost));
-    if (s->G) HIP_TRY(rows_d2h(s->G, D.G, 4, d, DS, s0, N));
+    if (s->G) HIP_TRY(rows_d2h(h, s->G, D.G, q));
     if (s->stuck) HIP_TRY(hipMemcpy(s->stuck, D.stuck + s0, N, hipMemcpyDeviceToHost));
     if (s->active) HIP_TRY(hipMemcpy(s->active, D.active + s0, N, hipMemcpyDeviceToHost));
     if (s->stuck_pre) HIP_TRY(hipMemcpy(s->stuck_pre, D.stuck_pre + s0, N, hipMemcpyDeviceToHost));
     if (s->removed) HIP_TRY(hipMemcpy(s->removed, D.removed + s0, N, hipMemcpyDeviceToHost));
-    if (s->trace)
+    if (s->trace && N == (size_t)D.NT)
+        HIP_TRY(hipMemcpy(s->trace, D.trace, N * ((size_t)q.n_conv + 1), hipMemcpyDeviceToHost));
+    else if (s->trace)
         HIP_TRY(hipMemcpy2D(s->trace, N, D.trace + s0, (size_t)D.NT, N, (size_t)q.n_conv + 1, hipMemcpyDeviceToHost));
     if (s->S || s->Y) {
         std::vector<float> tmp(N * mx * DS);
@@ -1124,12 +1147,13 @@ extern "C" int chisao_get_state(chisao_handle h, int problem, chisao_state *s) {
                     memcpy(dst + (i * m + j) * d, tmp.data() + (i * mx + j) * DS, sizeof(float) * d);
         }
     }
-    if (s->rho) HIP_TRY(rows_d2h(s->rho, D.rho, 4, m, mx, s0, N));
+    if (s->rho)
+        HIP_TRY(hipMemcpy2D(s->rho, m * 4, D.rho + s0 * mx, mx * 4, m * 4, N, hipMemcpyDeviceToHost));
     if (s->head) HIP_TRY(hipMemcpy(s->head, D.head + s0, sizeof(int) * N, hipMemcpyDeviceToHost));
     if (s->cnt) HIP_TRY(hipMemcpy(s->cnt, D.cnt + s0, sizeof(int) * N, hipMemcpyDeviceToHost));
     if (s->conv) HIP_TRY(hipMemcpy(s->conv, D.conv + s0, N, hipMemcpyDeviceToHost));
     if (s->Fg) HIP_TRY(hipMemcpy(s->Fg, D.Fg + s0, sizeof(float) * N, hipMemcpyDeviceToHost));
-    if (s->Wd) HIP_TRY(rows_d2h(s->Wd, D.Wd, 4, d, DS, s0, N));
+    if (s->Wd) HIP_TRY(rows_d2h(h, s->Wd, D.Wd, q));
     if (s->wvalid) HIP_TRY(hipMemcpy(s->wvalid, D.wvalid + s0, N, hipMemcpyDeviceToHost));
     Ctl c;
     HIP_TRY(hipMemcpy(&c, D.ctl + problem, sizeof c, hipMemcpyDeviceToHost));
@@ -1153,19 +1177,18 @@ extern "C" int chisao_set_state(chisao_handle h, int problem, const chisao_state
     HIP_TRY(hipSetDevice(h->device));
     HIP_TRY(hipStreamSynchronize(h->stream));
     if (s->X) {
-        std::vector<float> lo(d), hi(d);
-        HIP_TRY(hipMemcpy(lo.data(), q.lo, sizeof(float) * d, hipMemcpyDeviceToHost));
-        HIP_TRY(hipMemcpy(hi.data(), q.hi, sizeof(float) * d, hipMemcpyDeviceToHost));
         // NaN marks a sample whose objective cannot be evaluated (it leaves the
         // population at the next Phase 2); anything else must lie in the box
-        for (size_t i = 0; i < N * d; ++i)
-            if (!(isnan(s->X[i]) || (s->X[i] >= lo[i % d] && s->X[i] <= hi[i % d])))
-                return fail(CHISAO_E_INVAL, "sample %zu lies outside the box", i / d);
-        HIP_TRY(hipMemcpy2D(D.X + s0 * DS, DS * 4, s->X, d * 4, d * 4, N, hipMemcpyHostToDevice));
+        int first = -1;
+        HIP_TRY(hipMemcpyAsync(D.Gh + s0 * DS, s->X, sizeof(float) * N * d, hipMemcpyHostToDevice, h->stream));
+        if ((rc = first_outside(h, D.Gh + s0 * DS, q, true, &first))) return rc;
+        if (first >= 0) return fail(CHISAO_E_INVAL, "sample %d lies outside the box", first);
+        HIP_TRY(launch_unpack_rows(D.Gh + s0 * DS, (int)d, (int)DS, (int)N, D.X + s0 * DS, h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
     }
     if (s->stuck) HIP_TRY(hipMemcpy(D.stuck + s0, s->stuck, N, hipMemcpyHostToDevice));
     if (s->active) HIP_TRY(hipMemcpy(D.active + s0, s->active, N, hipMemcpyHostToDevice));
-    if (s->Wd) HIP_TRY(hipMemcpy2D(D.Wd + s0 * DS, DS * 4, s->Wd, d * 4, d * 4, N, hipMemcpyHostToDevice));
+    if (s->Wd) HIP_TRY(rows_h2d(h, D.Wd, s->Wd, q));
     if (s->wvalid) HIP_TRY(hipMemcpy(D.wvalid + s0, s->wvalid, N, hipMemcpyHostToDevice));
     Ctl c;
     HIP_TRY(hipMemcpy(&c, D.ctl + problem, sizeof c, hipMemcpyDeviceToHost));

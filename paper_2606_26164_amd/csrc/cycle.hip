@@ -1446,6 +1446,52 @@ hipError_t launch_width_list(const Dev &D, int p, int N, hipStream_t st) {
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// State transfer.  The host's arrays are dense (rows of d), the library's rows
+// DS apart.  A strided copy to or from pageable memory is carried out row by
+// row (16.8 MB of d = 64 rows took 0.42 s), so rows are gathered or scattered
+// here, at the rate of the memory, and cross the bus as one block (3 ms).
+// ---------------------------------------------------------------------------
+__global__ void pack_rows_kernel(const float *src, int DS, int d, long n, float *dst) {
+    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n * d; e += (long)gridDim.x * blockDim.x)
+        dst[e] = src[(e / d) * DS + e % d];
+}
+
+__global__ void unpack_rows_kernel(const float *src, int d, int DS, long n, float *dst) {
+    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n * d; e += (long)gridDim.x * blockDim.x)
+        dst[(e / d) * DS + e % d] = src[e];
+}
+
+// *first: the lowest row with a coordinate outside the box (a NaN passes with
+// nan_ok only)
+__global__ void box_check_kernel(const float *x, int d, long n, const float *lo, const float *hi, int nan_ok,
+                                 int *first) {
+    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n * d; e += (long)gridDim.x * blockDim.x) {
+        const float v = x[e];
+        const int c = (int)(e % d);
+        if (!((v >= lo[c] && v <= hi[c]) || (nan_ok && v != v))) atomicMin(first, (int)(e / d));
+    }
+}
+
+hipError_t launch_pack_rows(const float *src, int DS, int d, int n, float *dst, hipStream_t st) {
+    hipLaunchKernelGGL(pack_rows_kernel, dim3(grid_for((long)n * d, kBlock, 4096)), dim3(kBlock), 0, st, src, DS, d,
+                       (long)n, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_unpack_rows(const float *src, int d, int DS, int n, float *dst, hipStream_t st) {
+    hipLaunchKernelGGL(unpack_rows_kernel, dim3(grid_for((long)n * d, kBlock, 4096)), dim3(kBlock), 0, st, src, d, DS,
+                       (long)n, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_box_check(const float *x, int d, int n, const float *lo, const float *hi, bool nan_ok, int *first,
+                            hipStream_t st) {
+    hipLaunchKernelGGL(box_check_kernel, dim3(grid_for((long)n * d, kBlock, 4096)), dim3(kBlock), 0, st, x, d, (long)n,
+                       lo, hi, (int)nan_ok, first);
+    return hipGetLastError();
+}
+
 hipError_t launch_mode_list(const Dev &D, int p, int s0, int N, hipStream_t st) {
     (void)s0;
     hipLaunchKernelGGL(ordered_lists_kernel, dim3(1), dim3(kScanThreads), 0, st, D, p);

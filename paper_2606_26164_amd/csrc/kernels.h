@@ -102,6 +102,12 @@ hipError_t launch_step_size(const Dev &D, const float *Gsrc, int which, hipStrea
 hipError_t launch_hlc_update(const Dev &D, int step, hipStream_t st, const int *pids = nullptr, int np = 0);
 hipError_t launch_anti_update(const Dev &D, int step, hipStream_t st, const int *pids = nullptr, int np = 0);
 hipError_t launch_end_cycle(const Dev &D, int advance, hipStream_t st);
+// Rows of d floats: gathered from rows DS apart, scattered to them, and the
+// lowest row outside a box (atomicMin into *first).  All pointers device.
+hipError_t launch_pack_rows(const float *src, int DS, int d, int n, float *dst, hipStream_t st);
+hipError_t launch_unpack_rows(const float *src, int d, int DS, int n, float *dst, hipStream_t st);
+hipError_t launch_box_check(const float *x, int d, int n, const float *lo, const float *hi, bool nan_ok, int *first,
+                            hipStream_t st);
 hipError_t launch_mode_list(const Dev &D, int p, int s0, int N, hipStream_t st);
 hipError_t launch_width_list(const Dev &D, int p, int N, hipStream_t st);
 // Mode export of problem p: its stuck active samples in ascending index, rows
