@@ -1250,7 +1250,7 @@ extern "C" int chisao_mode_widths(chisao_handle h, int problem, float *w_out, in
 // The launches of an evaluation on caller memory: value and adjoint gradient
 // in one pass, or the value and the central-difference stencils.  `a` carries
 // the device descriptors; results go to f_dev / G_dev (either may be null).
-static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, const float *X_dev, int B, float *f_dev,
+static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, int K, const float *X_dev, int B, float *f_dev,
                                     float *G_dev, int grad_mode, hipStream_t st) {
     a.X = X_dev;
     a.x_stride = d;
@@ -1258,17 +1258,20 @@ static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, const
     a.ext_n = B;
     a.vc_kind = kVcOne;
     const long Vfd = 2 * d;
+    const long tiles = (B + 31) / 32;
     hipError_t e;
     if (grad_mode == CHISAO_GRAD_ADJOINT) {
         a.F_out = f_dev;
         a.G_out = G_dev;
-        a.max_tiles = (B + 31) / 32;
+        a.max_tiles = tiles;
+        a.dsplit = direct_split(DP, family, K, tiles);
         return launch_eval(a, DP, family, kDirect, false, G_dev != nullptr, st);
     }
     if (f_dev) {
         a.F_out = f_dev;
         a.G_out = nullptr;
-        a.max_tiles = (B + 31) / 32;
+        a.max_tiles = tiles;
+        a.dsplit = direct_split(DP, family, K, tiles);
         if ((e = launch_eval(a, DP, family, kDirect, false, false, st)) != hipSuccess) return e;
     }
     if (G_dev) {
@@ -1298,7 +1301,7 @@ extern "C" int chisao_eval(chisao_handle h, int problem, const float *X_dev, int
     c.split = q.xs != nullptr;
     c.pids = {problem};
     c.pids_dev = h->pid_seq + problem;
-    HIP_TRY(ext_eval_launches(base_args(h, c), q.d, q.DP, q.family, X_dev, B, f_dev, G_dev, grad_mode, h->stream));
+    HIP_TRY(ext_eval_launches(base_args(h, c), q.d, q.DP, q.family, q.K, X_dev, B, f_dev, G_dev, grad_mode, h->stream));
     return CHISAO_OK;
 }
 
@@ -1502,6 +1505,6 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     a.trial_next = -1;
     a.nz_kind = -1;
     a.split = two_part;
-    HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, X_dev, B, f_dev, G_dev, grad_mode, st));
+    HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, (int)K, X_dev, B, f_dev, G_dev, grad_mode, st));
     return CHISAO_OK;
 }

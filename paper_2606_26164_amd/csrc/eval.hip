@@ -11,9 +11,9 @@
 // gradient: 2 K d^2 MFMA flops per point whether or not the gradient is kept.
 //
 // Work layout: a tile of 32 points in two 16-point blocks per wave (direct
-// evaluations may take 16-point half tiles; four waves share a line-search
-// tile, each contracting a contiguous quarter of the components, and their
-// partial states are merged in wave order).  v_mfma_f32_16x16x4f32 computes U^T (DP x 16) = P' (DP x DP) *
+// evaluations may take 16-point half tiles; several waves share a line-search
+// tile or one of a small direct evaluation, each contracting a contiguous part
+// of the components, and their partial states are merged in wave order).  v_mfma_f32_16x16x4f32 computes U^T (DP x 16) = P' (DP x DP) *
 // Delta^T (DP x 16), P' the precision matrix with its rows permuted: lane l
 // supplies P[pi(16mb + l%16)][4ks + l/16] (A operand), pi(16mb + 4a + b) =
 // 4(4mb + b) + a, and delta[point l%16][4ks + l/16] (B operand), and receives
@@ -123,15 +123,16 @@ struct CompRegs {
 // Two-part contraction.  u = P delta with each operand as a sum of two f16
 // values, x = h + l, h = f16(x) and l = f16(x - h) (round to nearest): the
 // three products l_P h_d + h_P l_d + h_P h_d on the f16 matrix core (16 times
-// the rate of the float32 one), summed in float32; at DP = 32 the fourth,
-// l_P l_d, as well.  h and l hold 23 of the 24 significant bits of x, so a term
+// the rate of the float32 one), summed in float32; up to d = kTwoPartLowD the
+// fourth, l_P l_d, as well.  h and l hold 23 of the 24 significant bits of x, so a term
 // is off by about a rounding of float32, and a sum goes through 3 DP / 32
 // accumulations instead of DP / 4.  Measured against float64 (relative, 2-norm
 // over 4000 points and more, K = 3 to 128, both families): gradients 1.4e-7
 // where the float32 contraction gives 1.7e-7 (d = 64), 1.1e-7 against 1.2e-7
 // (d = 32), 0.93e-7 against 0.95e-7 (d = 20); values alike (6e-8).  Without
-// l_P l_d the d = 20 gradients were at 1.07e-7, and at d = 12 four products
-// gave 9e-8 against 7e-8: so kTwoPartMinD, and DP = 16 stays in float32.
+// l_P l_d the d = 20 gradients were at 1.07e-7 and those of d = 33 at 1.26e-7
+// (float32 1.21e-7), and at d = 12 four products gave 9e-8 against 7e-8: so
+// kTwoPartLowD, and DP = 16 stays in float32.
 //
 // What bounds it: the matrix core's rate under load (the products alone ran at
 // 1480 TFLOP/s) plus the vector instructions that split delta (two conversions
@@ -153,7 +154,7 @@ struct CompRegs {
 // point far outside the box carries a power of two of its own (1 for any other
 // point), so nothing overflows that would not in float32.
 // ---------------------------------------------------------------------------
-constexpr int kTwoPartMinD = 17;  // least dimension: stated above
+constexpr int kTwoPartMinD = 17, kTwoPartLowD = 48;
 constexpr int kTwoPartP = 12, kTwoPartX = 13, kTwoPartSpan = 10, kTwoPartRatio = 12, kTwoPartMaxB = 12;
 
 bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, const float *lo, const float *hi,
@@ -184,15 +185,15 @@ bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, c
     return true;
 }
 
-// The coordinate a lane of row g holds at position i of its KS = DP / 4: every
-// fourth one in the operand order of the float32 instruction (K = 4), KS in a
-// row for the f16 one (K = 32: a lane's eight operands of step s are positions
-// 8 s .. 8 s + 7).  In either order the accumulators of block mb, with the rows
-// of P permuted alike, are the lane's positions 4 mb .. 4 mb + 3.
-template <bool H16>
-__device__ __forceinline__ constexpr int lane_coord(int KS, int i, int g) {
-    return H16 ? KS * g + i : 4 * i + g;
-}
+// The coordinate a lane of row g holds at position i of its DP / 4: every
+// fourth one, the operand order of the float32 instruction (K = 4).  The f16
+// instruction (K = 32) takes a lane's positions 8 s .. 8 s + 7 in step s;
+// which coordinates those are is free as long as both operands agree, and this
+// choice spreads d < DP evenly over the rows (with 16 in a row per lane the
+// values of d = 33 were 14% further off, from longer chains in delta . u).
+// The accumulators of block mb, with the rows of P permuted alike, are the
+// lane's positions 4 mb .. 4 mb + 3.
+__device__ __forceinline__ constexpr int lane_coord(int i, int g) { return 4 * i + g; }
 
 // Eight values of a lane as two f16 parts.  neg1 is -1 in a scalar register
 // the compiler cannot see through, which makes h - x one v_fma_mix_f32 (with a
@@ -383,6 +384,24 @@ __device__ __forceinline__ long tiles_of(int count, int V, int ppw, int &jpw, in
 // one tile's pass over the components, takes about half as long.
 constexpr int kHalfTileMax = 128;
 
+// Direct evaluations of few points (caller memory) split a tile's components
+// too.  One wave alone goes through K components in a row, so such a launch
+// took one pass however few its points: 118 us for 1 to 8192 points at d = 64,
+// K = 128.  Up to 128 full tiles, eight waves take a half tile (16 points), at
+// most one workgroup per CU: 23 us for one point, 29 us for 4096.  Up to 512
+// tiles, four waves take a full tile, two waves per SIMD: 77 us against 128
+// for 16384 points; at 1024 tiles it is 161 against 149.  Narrower components
+// keep more waves per SIMD resident, so there four waves pay up to 1024 tiles
+// if there are components enough to share (d = 32: 60 us against 69 at K =
+// 128, 29.7 against 31.8 at 48, but 17.7 against 16.9 at 16; d = 16, K = 128:
+// 35.8 against 47.4).  Populations are left as they are: a problem's results
+// do not depend on how many samples are evaluated together.
+int direct_split(int DP, int family, int K, long tiles) {
+    if (family >= kFamClosed || DP == kAluDP) return 0;
+    if (tiles <= 128) return kSplitHalf;
+    return tiles <= 512 || (tiles <= 1024 && DP <= 32 && K >= 32) ? kSplitFull : 0;
+}
+
 // SPLIT waves share a tile: each contracts a contiguous part of the
 // components and the first (lead) wave merges the partial log-sum-exp states
 // in wave order, then runs the epilogue.  Line-search launches are small (a
@@ -397,9 +416,12 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
     constexpr bool ALU = !CLOSED && DP == kAluDP;
     constexpr int PPW = ALU ? kWave : kTilePts;
     constexpr int LD = DP + 1;  // padded row: conflict-free column reads
-    constexpr int NP = SPLIT > 1 ? SPLIT - 1 : 1;
-    __shared__ float s_pm[NP][NB][kWave], s_ps[NP][NB][kWave];       // partial max / sum of waves 1..
-    __shared__ float s_pg[(SPLIT > 1 && GRAD) ? NP * NB * KS : 1][kWave];  // partial gradient sums
+    // split direct evaluations: every wave's partial state goes through LDS and
+    // all waves merge; split line-search tiles: waves 1.. hand theirs to the first
+    constexpr bool DSPLIT = CENTER == kDirect && SPLIT > 1;
+    constexpr int NP = SPLIT == 1 ? 1 : (DSPLIT ? SPLIT : SPLIT - 1), NBP = HT ? 1 : NB;
+    __shared__ float s_pm[NP][NBP][kWave], s_ps[NP][NBP][kWave];             // partial max / sum
+    __shared__ float s_pg[(SPLIT > 1 && GRAD) ? NP * NBP * KS : 1][kWave];  // partial gradient sums
     __shared__ float s_pts[PPW * LD];
     __shared__ float s_g[GRAD ? PPW * LD : 1];
     __shared__ float s_f[PPW];
@@ -420,7 +442,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
     constexpr bool HALF = TRIAL && SPLIT > 1;
     // HT: half tiles throughout (direct evaluations; the autotuner's choice
     // for classes whose launches hold too few full tiles to fill the chip)
-    static_assert(!HT || (CENTER == kDirect && !FD && SPLIT == 1 && !CLOSED && !ALU), "half tiles: direct MFMA only");
+    static_assert(!HT || (CENTER == kDirect && !FD && !CLOSED && !ALU), "half tiles: direct MFMA only");
+    static_assert(!DSPLIT || (!FD && !CLOSED && !ALU), "split direct evaluations: MFMA only");
     __shared__ int s_pref2[HALF ? kMaxClass + 1 : 1];  // tile prefix in half tiles
     __shared__ float s_x0[TRIAL ? PPW * LD : 1];
     __shared__ float s_g0[TRIAL ? PPW * LD : 1];
@@ -811,14 +834,14 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             for (int nb = 0; nb < NB; ++nb) {
                 const float *row = s_pts + (nb * 16 + n) * LD;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) xB[nb][ks] = row[lane_coord<H16>(KS, ks, g)];
+                for (int ks = 0; ks < KS; ++ks) xB[nb][ks] = row[lane_coord(ks, g)];
             }
             if constexpr (H16) {
                 const gfloat *xs = as_global(pd.xs), *mu0 = as_global(pd.muB2) + g * KS;
                 float far[NB] = {};
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const float sc = xs[lane_coord<H16>(KS, ks, g)], c0 = mu0[ks];
+                    const float sc = xs[lane_coord(ks, g)], c0 = mu0[ks];
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         xB[nb][ks] *= sc;
@@ -905,7 +928,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             // (two-part problems) the lane's own block's factor of the quadratic form
             float kq_own = 1.0f;
             if constexpr (H16) kq_own = (g & 1) ? kqn[1] : kqn[0];
-            auto step = [&](const Regs &r, auto nba) {
+            auto step = [&](const Regs &r, auto nba, auto four) {
+                constexpr bool FOUR = decltype(four)::value;
                 constexpr int NBA = decltype(nba)::value;
                 f32x4 acc[NB][MB];
 #pragma unroll
@@ -939,9 +963,9 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                                     acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa[mb], b[nb], acc[nb][mb], 0, 0, 0);
                         };
                         __builtin_amdgcn_s_setprio(1);
-                        if constexpr (DP == 32) product(r.pa[1][s], bl);
-                        product(r.pa[1][s], bh);
+                        if constexpr (FOUR) product(r.pa[1][s], bl);
                         product(r.pa[0][s], bl);
+                        product(r.pa[1][s], bh);
                         product(r.pa[0][s], bh);
                         __builtin_amdgcn_s_setprio(0);
                     }
@@ -1073,10 +1097,10 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                         load(kb, ra);
                         for (int k = kb; k < ke; k += 2) {
                             load(min(k + 1, ke - 1), rb);
-                            step(ra, nba);
+                            step(ra, nba, std::true_type{});
                             if (k + 1 >= ke) break;
                             load(min(k + 2, ke - 1), ra);
-                            step(rb, nba);
+                            step(rb, nba, std::true_type{});
                         }
                     }
                     own_to_blocks(nba);
@@ -1090,11 +1114,15 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     run(AllBlocks{});
                 }
             } else {
-                auto run = [&](auto nba) {
+                auto loop = [&](auto nba, auto four) {
                     for (int k = kb; k < ke; ++k) {
                         load(k, ra);
-                        step(ra, nba);
+                        step(ra, nba, four);
                     }
+                };
+                auto run = [&](auto nba) {
+                    if (H16 && d <= kTwoPartLowD) loop(nba, std::integral_constant<bool, H16>{});
+                    else loop(nba, std::false_type{});
                     own_to_blocks(nba);
                 };
                 if constexpr (HALF) {
@@ -1106,7 +1134,48 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     run(AllBlocks{});
                 }
             }
-            if constexpr (SPLIT > 1) {
+            if constexpr (DSPLIT) {
+                // merge: m the largest reference, the sums scaled by 2^(m_v - m)
+                // and added in wave order; each wave takes its share of the
+                // coordinates.  A part without components has reference -inf
+                // and sum 0, one that met a NaN has sum NaN.
+                constexpr int NBM = HT ? 1 : NB;
+#pragma unroll
+                for (int nb = 0; nb < NBM; ++nb) {
+                    s_pm[wv][nb][lane] = mrun[nb];
+                    s_ps[wv][nb][lane] = srun[nb];
+                    if constexpr (GRAD)
+#pragma unroll
+                        for (int i = 0; i < KS; ++i) s_pg[(wv * NBM + nb) * KS + i][lane] = gacc[nb][i];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int nb = 0; nb < NBM; ++nb) {
+                    float m = -INFINITY, sm = 0.0f, av[SPLIT];
+#pragma unroll
+                    for (int v = 0; v < SPLIT; ++v) m = fmaxf(m, s_pm[v][nb][lane]);
+#pragma unroll
+                    for (int v = 0; v < SPLIT; ++v) {
+                        const float mv = s_pm[v][nb][lane], sv = s_ps[v][nb][lane];
+                        av[v] = (mv == -INFINITY && sv == 0.0f) ? 0.0f : __builtin_amdgcn_exp2f(mv - m);
+                        sm = fmaf(sv, av[v], sm);
+                    }
+                    const int pt = nb * 16 + n;
+                    if (wv == 0 && g == 0) s_f[pt] = (m + __log2f(sm)) * kLn2;
+                    if constexpr (GRAD) {
+                        const float inv = -1.0f / sm;
+                        for (int i = wv; i < KS; i += SPLIT) {
+                            const int c = lane_coord(i, g);
+                            float gv = 0.0f;
+#pragma unroll
+                            for (int v = 0; v < SPLIT; ++v) gv = fmaf(s_pg[(v * NBM + nb) * KS + i][lane], av[v], gv);
+                            gv *= inv;
+                            if constexpr (H16) gv *= as_global(pd.xs)[c] * kgn[nb];
+                            s_g[pt * LD + c] = gv;
+                        }
+                    }
+                }
+            } else if constexpr (SPLIT > 1) {
                 // merge: m = max(m0, m_v), s = s0 2^(m0-m) + s_v 2^(m_v-m), the
                 // gradient sums alike, for v = 1, 2, ... in order
                 if (!lead) {
@@ -1142,7 +1211,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             // ---- results to LDS --------------------------------------------
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                if (!lead || ((HALF || HT) && nb * 16 >= ppw)) break;
+                if (DSPLIT || !lead || ((HALF || HT) && nb * 16 >= ppw)) break;
                 const int pt = nb * 16 + n;
                 float f = (mrun[nb] + __log2f(srun[nb])) * kLn2;
                 if (noisy && g == 0 && s_s[pt] >= 0) f += noise_of(pt);
@@ -1151,7 +1220,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     const float inv = -1.0f / srun[nb];
 #pragma unroll
                     for (int i = 0; i < KS; ++i) {
-                        const int c = lane_coord<H16>(KS, i, g);
+                        const int c = lane_coord(i, g);
                         float gv = gacc[nb][i] * inv;
                         if constexpr (H16) gv *= as_global(pd.xs)[c] * kgn[nb];
                         s_g[pt * LD + c] = gv;
@@ -1165,8 +1234,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
         if constexpr (CENTER == kDirect && !FD) {
             if (lead && lane < PPW && s_s[lane] >= 0 && a.F_out) a.F_out[s_s[lane]] = s_f[lane];
             if constexpr (GRAD) {
-                if (lead && a.G_out)
-                    for (int e = lane; e < PPW * d; e += kWave) {
+                if (a.G_out)
+                    for (int e = threadIdx.x; e < PPW * d; e += kWave * SPLIT) {
                         const int pt = e / d, c = e % d, s = s_s[pt];
                         if (s >= 0) a.G_out[(size_t)s * os + c] = s_g[pt * LD + c];
                     }
@@ -1268,10 +1337,22 @@ static hipError_t dispatch_modes(const EvalArgs &a, int center, bool fd, bool gr
     hipLaunchKernelGGL((eval_kernel<DP, FAM, G, kDirect, false, 1, true, H16>), grid, block, 0, st, a)
 #define CHISAO_GO_SPLIT(C, G, F) \
     hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, S, false, H16>), grid, dim3(kWave * S), 0, st, a)
+#define CHISAO_GO_DSPLIT(G, N, HALF) \
+    hipLaunchKernelGGL((eval_kernel<DP, FAM, G, kDirect, false, N, HALF, H16>), grid, dim3(kWave * N), 0, st, a)
     constexpr bool kHalfOk = FAM < kFamClosed && DP != kAluDP;  // tiles of two MFMA column blocks
     if (center == kDirect) {
         if (fd) CHISAO_GO(kDirect, false, true);
-        else if (kHalfOk && a.half_tiles) {
+        else if (kHalfOk && a.dsplit) {
+            if constexpr (kHalfOk) {
+                if (a.dsplit == kSplitHalf) {
+                    if (grad) CHISAO_GO_DSPLIT(true, kSplitHalf, true);
+                    else CHISAO_GO_DSPLIT(false, kSplitHalf, true);
+                } else {
+                    if (grad) CHISAO_GO_DSPLIT(true, kSplitFull, false);
+                    else CHISAO_GO_DSPLIT(false, kSplitFull, false);
+                }
+            }
+        } else if (kHalfOk && a.half_tiles) {
             if constexpr (kHalfOk) {
                 if (grad) CHISAO_GO_HALF(true);
                 else CHISAO_GO_HALF(false);
@@ -1288,6 +1369,7 @@ static hipError_t dispatch_modes(const EvalArgs &a, int center, bool fd, bool gr
 #undef CHISAO_GO
 #undef CHISAO_GO_HALF
 #undef CHISAO_GO_SPLIT
+#undef CHISAO_GO_DSPLIT
     return hipGetLastError();
 }
 
@@ -1348,7 +1430,8 @@ hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool f
     if (a.n_cls > kMaxClass) return hipErrorInvalidValue;
     const long cap = a.grid_cap > 0 ? a.grid_cap : 8192;
     // max_tiles counts 32-point tiles; half tiles are twice as many
-    const long tiles = (center == kDirect && !fd && a.half_tiles) ? 2 * a.max_tiles : a.max_tiles;
+    const bool halves = a.half_tiles || a.dsplit == kSplitHalf;
+    const long tiles = (center == kDirect && !fd && halves) ? 2 * a.max_tiles : a.max_tiles;
     long g = tiles < cap ? tiles : cap;
     if (a.order == 1) g = (g + 7) / 8 * 8;  // whole rounds over the XCDs
     const dim3 grid((unsigned)g);
@@ -1384,7 +1467,7 @@ __device__ void two_part_tables(int d, int DP, int k, int lane, const float *A, 
     for (int s = 0; s < S; ++s)
         for (int mb = 0; mb < MB; ++mb)
             for (int j = 0; j < 8; ++j) {
-                const int row = lane_coord<true>(KS, 4 * mb + (rho & 3), rho >> 2), col = lane_coord<true>(KS, 8 * s + j, lane >> 4);
+                const int row = lane_coord(4 * mb + (rho & 3), rho >> 2), col = lane_coord(8 * s + j, lane >> 4);
                 float v = 0.0f;
                 // scaled by 2^(kTwoPartP - e_row - e_col) = 1 / (kq xs_row xs_col)
                 if (row < d && col < d)
@@ -1395,7 +1478,7 @@ __device__ void two_part_tables(int d, int DP, int k, int lane, const float *A, 
                 P[(size_t)S * MB * kWave * 8 + o] = l;
             }
     if (lane < DP) {
-        const int c = lane_coord<true>(KS, lane % KS, lane / KS);
+        const int c = lane_coord(lane % KS, lane / KS);
         muB[(size_t)k * DP + lane] = c < d ? mu[c] * xs[c] : 0.0f;
     }
 }

@@ -39,8 +39,15 @@ struct EvalArgs {
     int nz_kind;          // evaluation noise of noisy problems: -1 none, 0 one draw per value, 1 gate mean
     int half_tiles;       // direct value (+ gradient) launches of matrix-core classes: 16-point tiles
     uint32_t nz_base;     // noise sub-stream base (kind 0); the noise step is `step`
+    int dsplit;           // direct value (+ gradient) launches on caller memory: direct_split()
     int split;            // contract in two f16 parts (the problems have those tables)
 };
+
+// Waves a tile's components are split over in a direct evaluation of `tiles`
+// full tiles on caller memory: kSplitHalf (on 16-point tiles), kSplitFull, or 0
+// (one wave per tile).
+constexpr int kSplitHalf = 8, kSplitFull = 4;
+int direct_split(int DP, int family, int K, long tiles);
 
 // center: kDirect / kTrial / kProbe; fd: stencil around each centre;
 // grad: accumulate the adjoint gradient.
