@@ -27,7 +27,8 @@
 //
 // The closed-form test functions of Appendix D share the kernel's tiling,
 // point generation and epilogues; their value (and analytic gradient) is a
-// sum over coordinates evaluated on the VALU, two lanes per point.
+// sum over coordinates evaluated on the VALU, two lanes per point.  Their
+// central differences have a kernel of their own (closed_fd_kernel).
 #include <math.h>
 
 #include <type_traits>
@@ -241,47 +242,77 @@ __device__ __forceinline__ void pow20(float su, float &p20, float &p19) {
     p19 = s16 * s2 * su;
 }
 
+// The transcendental factors of coordinate c's term, which depend on x_c alone ...
+__device__ __forceinline__ void cf_factors(int fam, int c, float v, float &t1, float &t2) {
+    t1 = t2 = 0.0f;
+    switch (fam) {
+        case CHISAO_RASTRIGIN:
+        case CHISAO_ACKLEY: t1 = cospif(2.0f * v); break;
+        case CHISAO_SCHWEFEL: t1 = sinf(sqrtf(fabsf(v))); break;
+        case CHISAO_MICHALEWICZ: {
+            float p19;
+            // sin(i x^2 / pi) = sinpi(i x^2 / pi^2): exact range reduction
+            pow20(sinpif((float)(c + 1) * v * v * kInvPi2), t2, p19);
+            t1 = sinf(v);
+            break;
+        }
+    }
+}
+
+// ... and that term, added to the accumulators (prev: x_{c-1}, for c > 0).
+__device__ __forceinline__ void cf_add(int fam, int c, float v, float prev, float t1, float t2, float &a, float &b) {
+    switch (fam) {
+        case CHISAO_RASTRIGIN: a += v * v - 10.0f * t1; break;
+        case CHISAO_ACKLEY:
+            a += v * v;
+            b += t1;
+            break;
+        case CHISAO_SCHWEFEL: a += v * t1; break;
+        case CHISAO_STYBLINSKI_TANG: {
+            const float v2 = v * v;
+            a += v2 * v2 - 16.0f * v2 + 5.0f * v;
+            break;
+        }
+        case CHISAO_MICHALEWICZ: a += t1 * t2; break;
+        case CHISAO_TRID:
+            a += (v - 1.0f) * (v - 1.0f);
+            if (c > 0) b += v * prev;
+            break;
+    }
+}
+
+__device__ __forceinline__ float cf_bukin(float x0, float x1) {
+    return 100.0f * sqrtf(fabsf(x1 - 0.01f * x0 * x0)) + 0.01f * fabsf(x0 + 10.0f);
+}
+
+// f(std::integral_constant<int, fam>) for the functions that are sums over the
+// coordinates, so that loops over them hold one function's term and no switch
+template <class F>
+__device__ __forceinline__ void cf_dispatch(int fam, F &&f) {
+    switch (fam) {
+        case CHISAO_RASTRIGIN: f(std::integral_constant<int, CHISAO_RASTRIGIN>{}); break;
+        case CHISAO_ACKLEY: f(std::integral_constant<int, CHISAO_ACKLEY>{}); break;
+        case CHISAO_SCHWEFEL: f(std::integral_constant<int, CHISAO_SCHWEFEL>{}); break;
+        case CHISAO_STYBLINSKI_TANG: f(std::integral_constant<int, CHISAO_STYBLINSKI_TANG>{}); break;
+        case CHISAO_MICHALEWICZ: f(std::integral_constant<int, CHISAO_MICHALEWICZ>{}); break;
+        case CHISAO_TRID: f(std::integral_constant<int, CHISAO_TRID>{}); break;
+    }
+}
+
 __device__ __forceinline__ void cf_partial(int fam, int d, const float *x, int c0, float &a, float &b) {
     a = 0.0f;
     b = 0.0f;
-    switch (fam) {
-        case CHISAO_RASTRIGIN:
-            for (int c = c0; c < d; c += 2) a += x[c] * x[c] - 10.0f * cospif(2.0f * x[c]);
-            break;
-        case CHISAO_ACKLEY:
-            for (int c = c0; c < d; c += 2) {
-                a += x[c] * x[c];
-                b += cospif(2.0f * x[c]);
-            }
-            break;
-        case CHISAO_SCHWEFEL:
-            for (int c = c0; c < d; c += 2) a += x[c] * sinf(sqrtf(fabsf(x[c])));
-            break;
-        case CHISAO_STYBLINSKI_TANG:
-            for (int c = c0; c < d; c += 2) {
-                const float v = x[c], v2 = v * v;
-                a += v2 * v2 - 16.0f * v2 + 5.0f * v;
-            }
-            break;
-        case CHISAO_MICHALEWICZ:
-            for (int c = c0; c < d; c += 2) {
-                const float v = x[c];
-                float p20, p19;
-                // sin(i x^2 / pi) = sinpi(i x^2 / pi^2): exact range reduction
-                pow20(sinpif((float)(c + 1) * v * v * kInvPi2), p20, p19);
-                a += sinf(v) * p20;
-            }
-            break;
-        case CHISAO_TRID:
-            for (int c = c0; c < d; c += 2) {
-                a += (x[c] - 1.0f) * (x[c] - 1.0f);
-                if (c > 0) b += x[c] * x[c - 1];
-            }
-            break;
-        case CHISAO_BUKIN6:
-            if (c0 == 0) a = 100.0f * sqrtf(fabsf(x[1] - 0.01f * x[0] * x[0])) + 0.01f * fabsf(x[0] + 10.0f);
-            break;
+    if (fam == CHISAO_BUKIN6) {
+        if (c0 == 0) a = cf_bukin(x[0], x[1]);
+        return;
     }
+    cf_dispatch(fam, [&](auto fc) {
+        for (int c = c0; c < d; c += 2) {
+            float t1, t2;
+            cf_factors(fc.value, c, x[c], t1, t2);
+            cf_add(fc.value, c, x[c], c > 0 ? x[c - 1] : 0.0f, t1, t2, a, b);
+        }
+    });
 }
 
 __device__ __forceinline__ float cf_value(int fam, int d, float a, float b) {
@@ -1326,13 +1357,144 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
 }
 
 // ---------------------------------------------------------------------------
+// Central differences of the closed forms, one wave per centre (a sample, or a
+// smoothing probe of one) and one lane per stencil point.  A stencil point
+// differs from its centre in one coordinate, so the factors of its other d - 1
+// terms are the centre's: the wave takes them once, one lane per coordinate,
+// and each lane adds its point's terms from LDS, its own coordinate's in their
+// place, in the order the tiles add them (even coordinates, odd coordinates,
+// then the two): every value has the bits of a full evaluation of that point.
+//
+// What bounds it: the vector unit.  As tiles of 32 points, each with all its
+// terms, the d = 64 Michalewicz function spent 45 instructions a term and as
+// much again on the tile's own bookkeeping: 8192 gradients (and values) took
+// 150 us, with the factors shared within those tiles 103 us, here 26 us.
+// ---------------------------------------------------------------------------
+constexpr int kCfdWaves = 4;  // waves (centres at a time) per workgroup
+template <int CENTER>
+__global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a) {
+    __shared__ int s_pref[kMaxClass + 1];
+    __shared__ f32x4 s_row[kCfdWaves][kWave];  // per coordinate: centre, its two factors
+    const Dev &D = a.D;
+    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    const bool ext = a.ext_n >= 0;
+    if (wv == 0) {
+        int carry = 0;
+        if (lane == 0) s_pref[0] = 0;
+        for (int j0 = 0; j0 < a.n_cls; j0 += kWave) {
+            const int j = j0 + lane;
+            int t = 0;
+            if (j < a.n_cls) {
+                const int p = a.cls[j];
+                const ProblemDesc &pd = D.pd[p];
+                t = job_count(a, p, pd) * centres(a, pd);
+                if (blockIdx.x == 0 && !ext && t > 0) {
+                    const unsigned long long nv = (unsigned long long)t * (unsigned long long)(2 * pd.d);
+                    atomicAdd(&D.ctl[p].evals, nv);
+                    atomicAdd(&D.prof[CHISAO_PROF_EVAL_FD], nv);
+                }
+            }
+            const int inc = wave_scan(t);
+            if (j < a.n_cls) s_pref[j + 1] = carry + inc;
+            carry += __shfl(inc, kWave - 1, kWave);
+        }
+    }
+    __syncthreads();
+    const int total = s_pref[a.n_cls];
+    // (no barrier inside the loop: a wave's rows of s_row are its own)
+    for (int u = blockIdx.x * kCfdWaves + wv; u < total; u += gridDim.x * kCfdWaves) {
+        int lo_j = 0, hi_j = a.n_cls - 1;
+        while (lo_j < hi_j) {
+            const int mid = (lo_j + hi_j + 1) >> 1;
+            if (s_pref[mid] <= u) lo_j = mid;
+            else hi_j = mid - 1;
+        }
+        const int p = __builtin_amdgcn_readfirstlane(a.cls[lo_j]);
+        const ProblemDesc &pd = D.pd[p];
+        const int d = pd.d, fam = pd.family, Vc = centres(a, pd);
+        const int job = (u - s_pref[lo_j]) / Vc, ci = (u - s_pref[lo_j]) % Vc;
+        const int s = ext ? job : (a.list_id >= 0 ? list_ptr(D, a.list_id, pd.s0)[job] : pd.s0 + job);
+        const uint32_t kcyc = (uint32_t)D.ctl[p].k + 1u;
+        // the centre, one lane per coordinate
+        float xc = lane < d ? a.X[(size_t)s * a.x_stride + lane] : 0.0f;
+        if constexpr (CENTER == kProbe) {
+            float z[4];
+            box_muller4(philox((uint32_t)(s - pd.s0), kcyc, (kHLC << 24) | ((uint32_t)a.step << 16) | (uint32_t)(ci >> 1),
+                               (uint32_t)(lane >> 2), pd.key0, pd.key1),
+                        z);
+            const float zv = lane & 2 ? (lane & 1 ? z[3] : z[2]) : (lane & 1 ? z[1] : z[0]);
+            if (lane < d) xc = xc + D.ctl[p].sigma * ((ci & 1) ? -1.0f : 1.0f) * zv;
+        }
+        float t1 = 0.0f, t2 = 0.0f;
+        cf_dispatch(fam, [&](auto fc) { cf_factors(fc.value, lane, xc, t1, t2); });
+        s_row[wv][lane] = f32x4{xc, t1, t2, 0.0f};
+        __builtin_amdgcn_wave_barrier();
+        const float h = pd.fd_h > 0.0f ? pd.fd_h : ldexpf(fmaxf(1.0f, fabsf(xc)), -8);
+        const float up = xc + h, dn = xc - h;
+        for (int st0 = 0; st0 < 2 * d; st0 += kWave) {
+            const int st = st0 + lane, cs = min(st >> 1, d - 1);
+            const float xs_up = __shfl(up, cs, kWave), xs_dn = __shfl(dn, cs, kWave);
+            const float own = (st & 1) ? xs_dn : xs_up, den = xs_up - xs_dn;
+            float sa = 0.0f, sb = 0.0f;
+            if (fam == CHISAO_BUKIN6) {
+                sa = cf_bukin(cs == 0 ? own : s_row[wv][0][0], cs == 1 ? own : s_row[wv][1][0]);
+            } else {
+                cf_dispatch(fam, [&](auto fc) {
+                    float o1, o2, oa = 0.0f, ob = 0.0f, prev = 0.0f;
+                    cf_factors(fc.value, cs, own, o1, o2);
+                    auto add = [&](int c, float &ra, float &rb) {
+                        const f32x4 r = s_row[wv][c];
+                        const bool mine = c == cs;
+                        const float v = mine ? own : r[0];
+                        cf_add(fc.value, c, v, prev, mine ? o1 : r[1], mine ? o2 : r[2], ra, rb);
+                        prev = v;
+                    };
+                    int c = 0;
+#pragma unroll 4
+                    for (; c + 1 < d; c += 2) {
+                        add(c, sa, sb);
+                        add(c + 1, oa, ob);
+                    }
+                    if (c < d) add(c, sa, sb);
+                    sa += oa;
+                    sb += ob;
+                });
+            }
+            float f = cf_value(fam, d, sa, sb);
+            if (!ext && a.nz_kind >= 0 && pd.noise_sigma > 0.0f) {
+                uint32_t sub = a.nz_base;
+                if constexpr (CENTER == kProbe) sub |= (uint32_t)ci << 7;
+                sub += (uint32_t)st;
+                float z[4];
+                box_muller4(philox((uint32_t)(s - pd.s0), kcyc, (kNoise << 24) | ((uint32_t)a.step << 16) | sub, 0u,
+                                   pd.key0, pd.key1),
+                            z);
+                f += pd.noise_sigma * z[0];
+            }
+            const float f_dn = __shfl_xor(f, 1, kWave);
+            if (st < 2 * d && !(st & 1)) {
+                const float gv = (f - f_dn) / den;
+                if constexpr (CENTER == kDirect) a.G_out[(size_t)s * a.out_stride + cs] = gv;
+                else D.Gp[((size_t)s * D.Mmax + ci) * D.DS + cs] = gv;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Dispatch
 // ---------------------------------------------------------------------------
 template <int DP, int FAM, bool H16>
 static hipError_t dispatch_modes(const EvalArgs &a, int center, bool fd, bool grad, dim3 grid, hipStream_t st) {
     const dim3 block(kWave);
     constexpr int S = trial_split<DP, FAM>();
-#define CHISAO_GO(C, G, F) hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, 1, false, H16>), grid, block, 0, st, a)
+    constexpr bool kStencils = FAM < kFamClosed;  // (the closed forms' are closed_fd_kernel's)
+#define CHISAO_GO(C, G, F)                                                                             \
+    do {                                                                                               \
+        if constexpr (!(F) || kStencils)                                                               \
+            hipLaunchKernelGGL((eval_kernel<DP, FAM, G, C, F, 1, false, H16>), grid, block, 0, st, a); \
+    } while (0)
 #define CHISAO_GO_HALF(G) \
     hipLaunchKernelGGL((eval_kernel<DP, FAM, G, kDirect, false, 1, true, H16>), grid, block, 0, st, a)
 #define CHISAO_GO_SPLIT(C, G, F) \
@@ -1428,6 +1590,14 @@ static hipError_t dispatch_family(const EvalArgs &a, int fam, int center, bool f
 hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool fd, bool grad, hipStream_t st) {
     if (a.max_tiles <= 0 || a.n_cls <= 0) return hipSuccess;
     if (a.n_cls > kMaxClass) return hipErrorInvalidValue;
+    if (fd && family >= kFamClosed) {
+        // (a 32-point tile holds at most 16 centres)
+        const long need = (16 * a.max_tiles + kCfdWaves - 1) / kCfdWaves;
+        const dim3 g((unsigned)(need < 4096 ? need : 4096)), b(kWave * kCfdWaves);
+        if (center == kDirect) hipLaunchKernelGGL(closed_fd_kernel<kDirect>, g, b, 0, st, a);
+        else hipLaunchKernelGGL(closed_fd_kernel<kProbe>, g, b, 0, st, a);
+        return hipGetLastError();
+    }
     const long cap = a.grid_cap > 0 ? a.grid_cap : 8192;
     // max_tiles counts 32-point tiles; half tiles are twice as many
     const bool halves = a.half_tiles || a.dsplit == kSplitHalf;
