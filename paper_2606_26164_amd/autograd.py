@@ -22,7 +22,9 @@ class ChisaoLogDensity(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_out: torch.Tensor):
         (G,) = ctx.saved_tensors
-        return grad_out.to(G.dtype)[:, None] * G, None
+        if grad_out.dtype is not G.dtype:
+            grad_out = grad_out.to(G.dtype)
+        return G * grad_out.unsqueeze(1), None
 
 
 def log_density(X: torch.Tensor, opt) -> torch.Tensor:
