@@ -527,7 +527,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         ALLOC(D.status, uint8_t, N);
         ALLOC(D.reset, uint8_t, N);
         ALLOC(D.steep, uint8_t, N);
-        ALLOC(D.trace, uint8_t, N * (size_t)(ncmax + 1));
+        ALLOC(D.trace, uint8_t, (N * (size_t)(ncmax + 1) + 15) / 16 * 16);  // filled in 16-byte blocks
         ALLOC(D.S, float, N * (size_t)mmax * DSz);
         ALLOC(D.Y, float, N * (size_t)mmax * DSz);
         ALLOC(D.rho, float, N * (size_t)mmax);
@@ -818,59 +818,66 @@ static hipError_t eval_list_class(chisao_ctx *h, const EvalClass &c, hipStream_t
     return run_eval(h, c, a, kDirect, true, false, st);
 }
 
+// Small classes keep the active list through Phase 1 and pick the jobs of each
+// launch out of it by their flags.  Their launches are as long as their
+// latency, so a tile that is partly (or all) idle costs nothing, and the list
+// compactions, four of the eight launches of an iteration, would.  Per cycle: a
+// d = 6 problem of 256 samples 314 -> 283 us; K = 40, d = 8: 1.69 -> 1.47 ms
+// with 4096 samples, 1.91 -> 1.69 with 16384; K = 32, d = 16: 1.16 -> 1.09 with
+// 4096, but 1.43 -> 1.79 with 16384; wider ones gain nothing at 4096 and lose
+// from 8192 on (K = 48, d = 32: 1.50 -> 1.66): there the idle tiles of the later
+// search stages cost more than the compactions.
+static int in_place_max(int DP) { return DP == kAluDP ? 16384 : (DP == 16 ? 4096 : 2048); }
+
 // Iteration t of Phase 1 for one evaluation class, on the stream st (t runs
 // to the class's own n_conv + 1, which closes the last iteration).
 static hipError_t converge_iteration(chisao_ctx *h, const EvalClass &c, hipStream_t st, int t) {
     const Dev &D = h->D;
     const bool adj = c.grad_mode == CHISAO_GRAD_ADJOINT;
+    // (profiles tally the steppers in the compactions)
+    const bool in_place = c.n <= in_place_max(c.DP) && !h->prof;
     hipError_t e;
     // the steppers of iteration t go to list_out; t+1 reads them back
-    const int list_in = t == 1 ? L_ACT : ((t - 1) % 2 ? L_T1 : L_T1B);
-    const int list_out = t % 2 ? L_T1 : L_T1B;
-    if ((e = launch_reset_counts(D, (1 << list_out) | (1 << L_T2) | (1 << L_T3) | (1 << L_FD), st, c.pids_dev,
-                                 (int)c.pids.size())) != hipSuccess)
-        return e;
-    if ((e = timed(h, CHISAO_PROF_LBFGS,
-                   [&] { return launch_lbfgs_step(D, t, c.cpl, list_in, c.g0, c.n, st); })) != hipSuccess)
+    const int list_in = t == 1 || in_place ? L_ACT : ((t - 1) % 2 ? L_T1 : L_T1B);
+    const int list_out = in_place ? L_ACT : (t % 2 ? L_T1 : L_T1B);
+    const int reset = in_place ? 0 : (1 << list_out) | (1 << L_T2) | (1 << L_T3) | (1 << L_FD);
+    auto compact = [&](int src, int dst1, int dst2, bool count_fail, unsigned long long *tally = nullptr,
+                       unsigned long long *pairs = nullptr) {
+        return in_place ? hipSuccess : launch_compact(D, src, dst1, dst2, count_fail, tally, st, pairs, c.g0, c.n);
+    };
+    if ((e = timed(h, CHISAO_PROF_LBFGS, [&] {
+             return launch_lbfgs_step(D, t, c.cpl, list_in, in_place, reset, c.pids_dev, (int)c.pids.size(), c.g0, c.n,
+                                      st);
+         })) != hipSuccess)
         return e;
     if (t > c.nconv) return hipSuccess;
     // (the L-BFGS step and history-pair tallies are kept only when profiling)
-    if ((e = launch_compact(D, list_in, list_out, -1, false, h->prof ? D.prof + CHISAO_PROF_LBFGS : nullptr, st,
-                            h->prof ? D.prof + CHISAO_PROF_LBFGS_PAIRS : nullptr, c.g0, c.n)) != hipSuccess)
+    if ((e = compact(list_in, list_out, -1, false, h->prof ? D.prof + CHISAO_PROF_LBFGS : nullptr,
+                     h->prof ? D.prof + CHISAO_PROF_LBFGS_PAIRS : nullptr)) != hipSuccess)
         return e;
-    // first trial t = 1 for every stepper
-    {
-        EvalArgs a = base_args(h, c);
-        a.list_id = list_out;
-        a.vc_kind = kVcTrialFirst;
-        a.trial_next = L_T2;
-        a.step = t;
-        a.nz_kind = 0;
-        if ((e = run_eval(h, c, a, kTrial, false, adj, st)) != hipSuccess) return e;
-    }
-    if ((e = launch_compact(D, list_out, L_T2, L_FD, true, nullptr, st, nullptr, c.g0, c.n)) != hipSuccess) return e;
-    // the remaining trials in two stages: t = 1/2, 1/4, then the rest only
-    // for searches that rejected those too.  Most searches that reject t = 1
-    // accept one of the next two, so evaluating every remaining trial at once
-    // would mostly compute points that are never used.
-    for (int stage = 0; stage < 2; ++stage) {
-        const int lst = stage ? L_T3 : L_T2;
+    // first trial t = 1 for every stepper, then the remaining trials in two
+    // stages: t = 1/2, 1/4, then the rest only for searches that rejected
+    // those too.  Most searches that reject t = 1 accept one of the next two,
+    // so evaluating every remaining trial at once would mostly compute points
+    // that are never used.
+    for (int stage = 0; stage < 3; ++stage) {
+        const int lst = in_place ? L_ACT : (stage == 0 ? list_out : (stage == 1 ? L_T2 : L_T3));
         EvalArgs a = base_args(h, c);
         a.list_id = lst;
-        a.vc_kind = kVcTrialRest;
-        a.trial_lo = stage ? 3 : 1;
-        a.trial_cnt = stage ? kMaxTrials : 2;
-        a.trial_next = stage ? -1 : L_T3;
+        a.by_flag = in_place ? 1 : 0;
+        a.vc_kind = stage == 0 ? kVcTrialFirst : kVcTrialRest;
+        a.trial_lo = stage == 0 ? 0 : (stage == 1 ? 1 : 3);
+        a.trial_cnt = stage == 0 ? 0 : (stage == 1 ? 2 : kMaxTrials);
+        a.trial_next = stage == 0 ? L_T2 : (stage == 1 ? L_T3 : -1);
         a.step = t;
         a.nz_kind = 0;
         if ((e = run_eval(h, c, a, kTrial, false, adj, st)) != hipSuccess) return e;
-        if ((e = launch_compact(D, lst, stage ? -1 : L_T3, L_FD, true, nullptr, st, nullptr, c.g0, c.n)) !=
-            hipSuccess)
-            return e;
+        if ((e = compact(lst, a.trial_next, L_FD, true)) != hipSuccess) return e;
     }
     if (!adj) {
         EvalArgs b = base_args(h, c);
-        b.list_id = L_FD;
+        b.list_id = in_place ? L_ACT : L_FD;
+        b.by_flag = in_place ? 2 : 0;
         b.vc_kind = kVcOne;
         b.G_out = D.G;
         b.step = t;
@@ -992,7 +999,7 @@ static hipError_t enqueue_phases(chisao_ctx *h, uint32_t mask) {
     if (mask & (1u << 1))
         if ((e = phase_converge(h)) != hipSuccess) return e;
     if (mask & (1u << 2))
-        if ((e = launch_stick(D, st)) != hipSuccess) return e;
+        if ((e = launch_stick(D, h->any_noise, st)) != hipSuccess) return e;
     if (mask & (1u << 3))
         if ((e = launch_dedup(D, st)) != hipSuccess) return e;
     if (mask & (1u << 4))

@@ -101,6 +101,12 @@ __global__ void begin_ctl_kernel(Dev D) {
 }
 
 __global__ void begin_samples_kernel(Dev D) {
+    // the decision trace starts empty: (n_conv_max + 1) NT bytes, 16 at a time
+    // (its allocation is a whole number of 16-byte blocks)
+    const size_t blocks16 = ((size_t)(D.n_conv_max + 1) * D.NT + 15) / 16;
+    static_assert(kTrNone == 0xFF, "filled with all-ones words");
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < blocks16; i += (size_t)gridDim.x * blockDim.x)
+        reinterpret_cast<uint4 *>(D.trace)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
     // the loop bound is uniform per wave: the list appends are wave-wide
     for (int b = blockIdx.x * blockDim.x; b < D.NT; b += gridDim.x * blockDim.x) {
         const int s = b + threadIdx.x;
@@ -126,9 +132,7 @@ __global__ void begin_samples_kernel(Dev D) {
 hipError_t launch_begin_cycle(const Dev &D, hipStream_t st) {
     hipLaunchKernelGGL(begin_ctl_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
     hipLaunchKernelGGL(begin_samples_kernel, dim3(grid_for(D.NT, kBlock)), dim3(kBlock), 0, st, D);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_fill_u8(D.trace, kTrNone, (size_t)(D.n_conv_max + 1) * D.NT, st);
+    return hipGetLastError();
 }
 
 // the problems pids[0 .. np) (pids null: problems 0 .. np)
@@ -138,13 +142,6 @@ __global__ void reset_counts_kernel(Dev D, int mask, const int *pids, int np) {
     const int p = pids ? pids[i] : i;
     for (int l = 0; l < kNumLists; ++l)
         if (mask & (1 << l)) D.ctl[p].count[l] = 0;
-}
-
-hipError_t launch_reset_counts(const Dev &D, int mask, hipStream_t st, const int *pids, int np) {
-    const int n = pids ? np : D.P;
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(reset_counts_kernel, dim3(grid_for(n, 64)), dim3(64), 0, st, D, mask, pids, n);
-    return hipGetLastError();
 }
 
 // List compaction.  A block takes 256 consecutive list positions; per problem
@@ -311,7 +308,12 @@ __device__ __forceinline__ float row_dot(const float a[CPL], const float b[CPL])
 }
 
 template <int MM, int CPL>
-__global__ __launch_bounds__(kBlock) void lbfgs_step_kernel(Dev D, int t, int list_in, int g0, int n) {
+__global__ __launch_bounds__(kBlock) void lbfgs_step_kernel(Dev D, int t, int list_in, int in_place, int reset_mask,
+                                                            const int *pids, int np, int g0, int n) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < np; i += kBlock)
+            for (int l = 0; l < kNumLists; ++l)
+                if (reset_mask & (1 << l)) D.ctl[pids[i]].count[l] = 0;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x / kWave;
     const int rr = lane >> 4, l16 = lane & 15;
@@ -325,6 +327,10 @@ __global__ __launch_bounds__(kBlock) void lbfgs_step_kernel(Dev D, int t, int li
         if (pos < g0 + n) {
             p = D.pid[pos];
             if (pos - D.pd[p].s0 < D.ctl[p].count[list_in]) s = D.lists[(size_t)list_in * D.NT + pos];
+            if (in_place && t > 1 && s >= 0 && D.status[s] == 0) {  // took no step
+                if (l16 == 0) D.flag[pos] = 0;
+                s = -1;
+            }
         }
         if (__ballot(s >= 0) == 0) continue;
         const bool act = s >= 0 && D.active[s];
@@ -475,21 +481,23 @@ __global__ __launch_bounds__(kBlock) void lbfgs_step_kernel(Dev D, int t, int li
     }
 }
 
-template <int CPL>
-static void launch_lbfgs_cpl(const Dev &D, int t, int li, int g0, int n, hipStream_t st) {
+template <int CPL, class... Args>
+static void launch_lbfgs_cpl(const Dev &D, int n, hipStream_t st, Args... args) {
     const dim3 grid(grid_for((n + 3) / 4, kWavesPerBlock, 8192)), block(kBlock);
-    if (D.mmax <= 4) hipLaunchKernelGGL((lbfgs_step_kernel<4, CPL>), grid, block, 0, st, D, t, li, g0, n);
-    else if (D.mmax <= 8) hipLaunchKernelGGL((lbfgs_step_kernel<8, CPL>), grid, block, 0, st, D, t, li, g0, n);
-    else if (D.mmax <= 12) hipLaunchKernelGGL((lbfgs_step_kernel<12, CPL>), grid, block, 0, st, D, t, li, g0, n);
-    else if (D.mmax <= 16) hipLaunchKernelGGL((lbfgs_step_kernel<16, CPL>), grid, block, 0, st, D, t, li, g0, n);
-    else hipLaunchKernelGGL((lbfgs_step_kernel<32, CPL>), grid, block, 0, st, D, t, li, g0, n);
+    if (D.mmax <= 4) hipLaunchKernelGGL((lbfgs_step_kernel<4, CPL>), grid, block, 0, st, D, args...);
+    else if (D.mmax <= 8) hipLaunchKernelGGL((lbfgs_step_kernel<8, CPL>), grid, block, 0, st, D, args...);
+    else if (D.mmax <= 12) hipLaunchKernelGGL((lbfgs_step_kernel<12, CPL>), grid, block, 0, st, D, args...);
+    else if (D.mmax <= 16) hipLaunchKernelGGL((lbfgs_step_kernel<16, CPL>), grid, block, 0, st, D, args...);
+    else hipLaunchKernelGGL((lbfgs_step_kernel<32, CPL>), grid, block, 0, st, D, args...);
 }
 
-hipError_t launch_lbfgs_step(const Dev &D, int t, int cpl, int list_in, int g0, int n, hipStream_t st) {
+hipError_t launch_lbfgs_step(const Dev &D, int t, int cpl, int list_in, bool in_place, int reset_mask, const int *pids,
+                             int np, int g0, int n, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    if (cpl <= 1) launch_lbfgs_cpl<1>(D, t, list_in, g0, n, st);
-    else if (cpl <= 2) launch_lbfgs_cpl<2>(D, t, list_in, g0, n, st);
-    else launch_lbfgs_cpl<4>(D, t, list_in, g0, n, st);
+    const int ip = in_place;
+    if (cpl <= 1) launch_lbfgs_cpl<1>(D, n, st, t, list_in, ip, reset_mask, pids, np, g0, n);
+    else if (cpl <= 2) launch_lbfgs_cpl<2>(D, n, st, t, list_in, ip, reset_mask, pids, np, g0, n);
+    else launch_lbfgs_cpl<4>(D, n, st, t, list_in, ip, reset_mask, pids, np, g0, n);
     return hipGetLastError();
 }
 
@@ -593,11 +601,11 @@ __global__ void stick_kernel(Dev D) {
     }
 }
 
-hipError_t launch_stick(const Dev &D, hipStream_t st) {
+hipError_t launch_stick(const Dev &D, bool any_noise, hipStream_t st) {
     const dim3 grid(grid_for(D.NT / D.P + 1, kBlock, 256), D.P), block(kBlock);
     hipLaunchKernelGGL(stick_reset_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
     hipLaunchKernelGGL(fmax_kernel, grid, block, 0, st, D);
-    hipLaunchKernelGGL(fmax_redraw_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
+    if (any_noise) hipLaunchKernelGGL(fmax_redraw_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
     hipLaunchKernelGGL(stick_kernel, grid, block, 0, st, D);
     return hipGetLastError();
 }
@@ -652,12 +660,19 @@ __device__ __forceinline__ uint32_t hash_bucket(int cell, int lb) {
     return lb == 0 ? 0u : ((uint32_t)cell * 0x9E3779B1u) >> (32 - lb);
 }
 
+// Phase 3's starting state: no sample removed, counters and buckets empty.
 __global__ void dedup_clear_kernel(Dev D) {
     const int p = blockIdx.y;
     const ProblemDesc &pd = D.pd[p];
     int *cnt = D.hoff + pd.hk0;
     const int nb = (1 << pd.hash_lb) + 1;
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += gridDim.x * blockDim.x) cnt[b] = 0;
+    const int i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    if (i0 == 0) {
+        D.ctl[p].K_lost = 0;
+        D.ctl[p].n_modes = 0;
+    }
+    for (int b = i0; b < nb; b += step) cnt[b] = 0;
+    for (int i = i0; i < pd.N; i += step) D.removed[pd.s0 + i] = 0;
 }
 
 __global__ void dedup_count_kernel(Dev D) {
@@ -768,17 +783,6 @@ __global__ __launch_bounds__(kBlock) void dedup_scan_kernel(Dev D) {
     }
 }
 
-__global__ void dedup_reset_kernel(Dev D) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= D.P) return;
-    D.ctl[p].K_lost = 0;
-    D.ctl[p].n_modes = 0;
-}
-
-__global__ void clear_removed_kernel(Dev D) {
-    for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < D.NT; s += gridDim.x * blockDim.x) D.removed[s] = 0;
-}
-
 __global__ void dedup_finalize_kernel(Dev D) {
     for (int b = blockIdx.x * blockDim.x; b < D.NT; b += gridDim.x * blockDim.x) {
         const int s = b + threadIdx.x;
@@ -803,12 +807,25 @@ __global__ void dedup_finalize_kernel(Dev D) {
 // Phase 1 are recomputed: a sample that was stuck before is released with an
 // empty history and sticks again without a step, so it keeps the diagonal it
 // had; a survivor that never had a pair gets gamma0 = 1 / max(|g|_2, 1).
+// Golden Rooster generations: a generation that found no new peak counts
+// as a failure; two in a row disable it for the rest of the run.
+__device__ void gr_book(Ctl *c) {
+    if (c->gr_used_last) {
+        if (c->n_modes <= c->gr_prev_modes) c->gr_fail += 1;
+        else c->gr_fail = 0;
+        if (c->gr_fail >= 2) c->gr_disabled = 1;
+        c->gr_used_last = 0;
+    }
+}
+
 constexpr int kWidthBlock = 256;
 __global__ __launch_bounds__(kWidthBlock) void width_kernel(Dev D) {
     __shared__ float H[64 * 64];
     __shared__ float sv[64], yv[64], wv[64];
     __shared__ float red[kWidthBlock];
     const int tid = threadIdx.x;
+    if (blockIdx.x == 0)
+        for (int p = tid; p < D.P; p += kWidthBlock) gr_book(&D.ctl[p]);
     for (int s = blockIdx.x; s < D.NT; s += gridDim.x) {
         if (!(D.stuck[s] && D.active[s])) continue;
         const ProblemDesc &pd = D.pd[D.pid[s]];
@@ -890,23 +907,7 @@ __global__ __launch_bounds__(kWidthBlock) void width_kernel(Dev D) {
     }
 }
 
-// Golden Rooster generations: a generation that found no new peak counts
-// as a failure; two in a row disable it for the rest of the run.
-__global__ void gr_book_kernel(Dev D) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= D.P) return;
-    Ctl *c = &D.ctl[p];
-    if (c->gr_used_last) {
-        if (c->n_modes <= c->gr_prev_modes) c->gr_fail += 1;
-        else c->gr_fail = 0;
-        if (c->gr_fail >= 2) c->gr_disabled = 1;
-        c->gr_used_last = 0;
-    }
-}
-
 hipError_t launch_dedup(const Dev &D, hipStream_t st) {
-    hipLaunchKernelGGL(dedup_reset_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
-    hipLaunchKernelGGL(clear_removed_kernel, dim3(grid_for(D.NT, kBlock, 1024)), dim3(kBlock), 0, st, D);
     const dim3 per_sample(grid_for(D.NT / D.P + 1, kBlock, 256), D.P);
     const dim3 per_wave(grid_for(D.NT / D.P + 1, kBlock / kWave, 4096), D.P);
     hipLaunchKernelGGL(dedup_clear_kernel, dim3(grid_for(D.NT / D.P + 2, kBlock, 256), D.P), dim3(kBlock), 0, st, D);
@@ -916,7 +917,6 @@ hipError_t launch_dedup(const Dev &D, hipStream_t st) {
     hipLaunchKernelGGL(dedup_scan_kernel, per_wave, dim3(kBlock), 0, st, D);
     hipLaunchKernelGGL(dedup_finalize_kernel, dim3(grid_for(D.NT, kBlock, 1024)), dim3(kBlock), 0, st, D);
     hipLaunchKernelGGL(width_kernel, dim3(grid_for(D.NT, 1, 2048)), dim3(kWidthBlock), 0, st, D);
-    hipLaunchKernelGGL(gr_book_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
     return hipGetLastError();
 }
 
@@ -932,7 +932,10 @@ __global__ __launch_bounds__(kScanThreads) void ordered_lists_kernel(Dev D, int 
     __shared__ int sc[3][kScanThreads];
     const int p = only_p >= 0 ? only_p : blockIdx.x;
     const ProblemDesc &pd = D.pd[p];
-    if (only_p < 0 && (D.ctl[p].K_lost == 0 || !((pd.phase_mask >> 4) & 1))) return;
+    if (only_p < 0 && (D.ctl[p].K_lost == 0 || !((pd.phase_mask >> 4) & 1))) {
+        if (threadIdx.x == 0) D.ctl[p].reseed_kind = 0;
+        return;
+    }
     const int tid = threadIdx.x;
     const int chunk = (pd.N + kScanThreads - 1) / kScanThreads;
     const int b = pd.s0 + tid * chunk, e = min(pd.s0 + pd.N, b + chunk);
@@ -971,22 +974,12 @@ __global__ __launch_bounds__(kScanThreads) void ordered_lists_kernel(Dev D, int 
         D.ctl[p].count[O_SLOTS] = sc[0][tid];
         D.ctl[p].count[O_FREE] = sc[1][tid];
         D.ctl[p].count[O_PEAKS] = sc[2][tid];
+        // Repulse Monkey when at least five unfrozen samples remain, Golden
+        // Rooster otherwise (unless disabled), else the slots leave the
+        // population
+        if (only_p < 0)
+            D.ctl[p].reseed_kind = sc[1][tid] >= 5 ? 1 : (!D.ctl[p].gr_disabled && sc[2][tid] > 0 ? 2 : 3);
     }
-}
-
-// Repulse Monkey when at least five unfrozen samples remain, Golden Rooster
-// otherwise (unless disabled), else the slots are taken out of use.
-__global__ void reseed_decide_kernel(Dev D) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= D.P) return;
-    Ctl *c = &D.ctl[p];
-    if (c->K_lost == 0 || !((D.pd[p].phase_mask >> 4) & 1)) {
-        c->reseed_kind = 0;
-        return;
-    }
-    if (c->count[O_FREE] >= 5) c->reseed_kind = 1;
-    else if (!c->gr_disabled && c->count[O_PEAKS] > 0) c->reseed_kind = 2;
-    else c->reseed_kind = 3;
 }
 
 // Shared ray step: x = o + frac * t_max * u, t_max the distance to the box
@@ -1008,9 +1001,23 @@ __device__ __forceinline__ void ray_fill(const Dev &D, const ProblemDesc &pd, in
     }
 }
 
+// A removed slot's sample starts over, or (kind 3) leaves the population; one
+// wave.  removed[] keeps the deduplication decisions until the next cycle.
+__device__ __forceinline__ void slot_done(const Dev &D, const ProblemDesc &pd, int kind, int s, int lane) {
+    if (lane == 0) {
+        if (kind == 3) D.active[s] = 0;
+        D.stuck[s] = 0;
+        D.cnt[s] = 0;
+        D.head[s] = pd.m - 1;
+        D.wvalid[s] = 0;
+    }
+    if (lane < pd.d) D.V[(size_t)s * D.DS + lane] = 0.0f;
+}
+
 __global__ __launch_bounds__(kBlock) void rm_kernel(Dev D) {
     const int p = blockIdx.y;
-    if (D.ctl[p].reseed_kind != 1) return;
+    const int kind = D.ctl[p].reseed_kind;
+    if (kind != 1 && kind != 3) return;
     const ProblemDesc &pd = D.pd[p];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int nslots = D.ctl[p].count[O_SLOTS], nfree = D.ctl[p].count[O_FREE];
@@ -1018,6 +1025,8 @@ __global__ __launch_bounds__(kBlock) void rm_kernel(Dev D) {
     const int *slots = list_ptr(D, O_SLOTS, pd.s0), *freel = list_ptr(D, O_FREE, pd.s0);
     for (int j = blockIdx.x * kWavesPerBlock + wv; j < nslots; j += gridDim.x * kWavesPerBlock) {
         const int s = slots[j];
+        slot_done(D, pd, kind, s, lane);
+        if (kind == 3) continue;
         const uint32_t sl = (uint32_t)(s - pd.s0);
         const uint4 o4 = philox(sl, k, kRM << 24, 0u, pd.key0, pd.key1);
         const int origin = freel[uint_below(o4.x, (uint32_t)nfree)];
@@ -1047,8 +1056,13 @@ __global__ __launch_bounds__(kWave) void gr_kernel(Dev D) {
     const int nslots = D.ctl[p].count[O_SLOTS], np = D.ctl[p].count[O_PEAKS];
     const uint32_t k = (uint32_t)D.ctl[p].k + 1u;
     const int *slots = list_ptr(D, O_SLOTS, pd.s0), *peaks = list_ptr(D, O_PEAKS, pd.s0);
+    if (blockIdx.x == 0 && lane == 0) {
+        D.ctl[p].gr_used_last = 1;
+        D.ctl[p].gr_prev_modes = D.ctl[p].n_modes;
+    }
     for (int j = blockIdx.x; j < nslots; j += gridDim.x) {
         const int s = slots[j];
+        slot_done(D, pd, 2, s, lane);
         const int q = j % np, use = j / np;
         const int col = (use / 2) % d;
         const float sgn = (use & 1) ? -1.0f : 1.0f;
@@ -1107,36 +1121,11 @@ __global__ __launch_bounds__(kWave) void gr_kernel(Dev D) {
     }
 }
 
-__global__ void reseed_finalize_kernel(Dev D) {
-    const int p = blockIdx.y;
-    const int kind = D.ctl[p].reseed_kind;
-    if (kind == 0) return;
-    const ProblemDesc &pd = D.pd[p];
-    const int nslots = D.ctl[p].count[O_SLOTS];
-    const int *slots = list_ptr(D, O_SLOTS, pd.s0);
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < nslots; j += gridDim.x * blockDim.x) {
-        const int s = slots[j];
-        if (kind == 3) D.active[s] = 0;
-        D.stuck[s] = 0;  // removed[] keeps the deduplication decisions until the next cycle
-        D.cnt[s] = 0;
-        D.head[s] = pd.m - 1;
-        D.wvalid[s] = 0;
-        for (int c = 0; c < pd.d; ++c) D.V[(size_t)s * D.DS + c] = 0.0f;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && kind == 2) {
-        D.ctl[p].gr_used_last = 1;
-        D.ctl[p].gr_prev_modes = D.ctl[p].n_modes;
-    }
-}
-
 hipError_t launch_reseed(const Dev &D, hipStream_t st) {
     const unsigned per = grid_for(D.NT / D.P + 1, kWavesPerBlock, 1024);
     hipLaunchKernelGGL(ordered_lists_kernel, dim3(D.P), dim3(kScanThreads), 0, st, D, -1);
-    hipLaunchKernelGGL(reseed_decide_kernel, dim3(grid_for(D.P, 64)), dim3(64), 0, st, D);
     hipLaunchKernelGGL(rm_kernel, dim3(per, D.P), dim3(kBlock), 0, st, D);
     hipLaunchKernelGGL(gr_kernel, dim3(grid_for(D.NT / D.P + 1, 1, 2048), D.P), dim3(kWave), 0, st, D);
-    hipLaunchKernelGGL(reseed_finalize_kernel, dim3(grid_for(D.NT / D.P + 1, kBlock, 256), D.P), dim3(kBlock), 0, st,
-                       D);
     return hipGetLastError();
 }
 

@@ -476,6 +476,9 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
     static_assert(!HT || (CENTER == kDirect && !FD && !CLOSED && !ALU), "half tiles: direct MFMA only");
     static_assert(!DSPLIT || (!FD && !CLOSED && !ALU), "split direct evaluations: MFMA only");
     __shared__ int s_pref2[HALF ? kMaxClass + 1 : 1];  // tile prefix in half tiles
+    // jobs picked out of a list by their flag: launches of Phase 1 only
+    constexpr bool FLAGS = TRIAL || (FD && CENTER == kDirect);
+    __shared__ int s_live[1];
     __shared__ float s_x0[TRIAL ? PPW * LD : 1];
     __shared__ float s_g0[TRIAL ? PPW * LD : 1];
     __shared__ float s_dp[TRIAL ? PPW * KS : 1];
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                     t = (int)tiles_of(jobs, V, PPW, jpw, wpj);
                     if constexpr (HALF) t2 = (int)tiles_of(jobs, V, PPW / 2, jpw, wpj);
                     // evaluation counts, once per launch (block 0) rather than per tile
-                    if (blockIdx.x == 0 && !ext && jobs > 0) {
+                    if (blockIdx.x == 0 && !ext && jobs > 0 && !(FLAGS && a.by_flag)) {
                         const unsigned long long nv = (unsigned long long)jobs * (unsigned long long)V;
                         atomicAdd(&D.ctl[p].evals, nv);
                         atomicAdd(&D.prof[FD ? 3 : CENTER], nv);
@@ -537,7 +540,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             acc += (int)tiles_of(jobs, centres(a, pd) * Vs, HT ? PPW / 2 : PPW, jpw, wpj);
             s_pref[j + 1] = acc;
             // evaluation counts, once per launch (block 0) rather than per tile
-            if (blockIdx.x == 0 && !ext && jobs > 0) {
+            if (blockIdx.x == 0 && !ext && jobs > 0 && !(FLAGS && a.by_flag)) {
                 const unsigned long long nv = (unsigned long long)jobs * centres(a, pd) * Vs;
                 atomicAdd(&D.ctl[p].evals, nv);
                 pts += nv;
@@ -605,12 +608,31 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                 v = (int)(ltile % wpj) * ppw + pt;
                 valid = pt < ppw && v < V;
             }
+            if constexpr (FLAGS) {
+                if (a.by_flag) {
+                    valid = valid && D.flag[pd.s0 + job] == a.by_flag;
+                    // the points of this tile, counted here (below: lanes < PPW)
+                    const int n = (int)__popcll(__ballot(valid));
+                    if (lane == 0) {
+                        s_live[0] = n;
+                        if (n) {
+                            atomicAdd(&D.ctl[p].evals, (unsigned long long)n);
+                            atomicAdd(&D.prof[FD ? 3 : CENTER], (unsigned long long)n);
+                        }
+                    }
+                }
+            }
             s_s[pt] = valid ? (ext ? job : (lst ? lst[job] : pd.s0 + job)) : -1;
             s_c[pt] = v / Vs;
             s_st[pt] = v % Vs;
             s_den[pt] = 1.0f;
         }
         __syncthreads();
+        if constexpr (FLAGS)
+            if (a.by_flag && s_live[0] == 0) {
+                __syncthreads();
+                continue;
+            }
         // ---- generate the points (zero padded to DP), all waves -------------
         // rows are read in 16-byte chunks when the row stride and base allow it
         // (the library's own rows always do; a caller's array may not)
@@ -1349,6 +1371,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
                         verdict = 3;
                     }
                     D.flag[pd.s0 + (int)(ltile * jpw) + lane] = verdict;
+                    // (the compaction counts the failed searches otherwise)
+                    if (a.by_flag && verdict == 3) atomicAdd(&D.ctl[p].ls_fail, 1);
                 }
             }
         }
@@ -1388,7 +1412,7 @@ __global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a)
                 const int p = a.cls[j];
                 const ProblemDesc &pd = D.pd[p];
                 t = job_count(a, p, pd) * centres(a, pd);
-                if (blockIdx.x == 0 && !ext && t > 0) {
+                if (blockIdx.x == 0 && !ext && t > 0 && !a.by_flag) {
                     const unsigned long long nv = (unsigned long long)t * (unsigned long long)(2 * pd.d);
                     atomicAdd(&D.ctl[p].evals, nv);
                     atomicAdd(&D.prof[CHISAO_PROF_EVAL_FD], nv);
@@ -1415,6 +1439,13 @@ __global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a)
         const int job = (u - s_pref[lo_j]) / Vc, ci = (u - s_pref[lo_j]) % Vc;
         const int s = ext ? job : (a.list_id >= 0 ? list_ptr(D, a.list_id, pd.s0)[job] : pd.s0 + job);
         const uint32_t kcyc = (uint32_t)D.ctl[p].k + 1u;
+        if (a.by_flag) {
+            if (D.flag[pd.s0 + job] != a.by_flag) continue;
+            if (lane == 0) {
+                atomicAdd(&D.ctl[p].evals, (unsigned long long)(2 * d));
+                atomicAdd(&D.prof[CHISAO_PROF_EVAL_FD], (unsigned long long)(2 * d));
+            }
+        }
         // the centre, one lane per coordinate
         float xc = lane < d ? a.X[(size_t)s * a.x_stride + lane] : 0.0f;
         if constexpr (CENTER == kProbe) {

@@ -25,6 +25,7 @@ struct EvalArgs {
     int x_stride;         // DS for the population, d for caller memory
     int ext_n;            // >= 0: caller memory, jobs 0..ext_n-1 of problem cls[0]; -1: population lists
     int list_id;          // population jobs: list id, or -1 for every sample of the problem
+    int by_flag;          // > 0: of the list, only positions with D.flag == by_flag (line searches, Phase 1 stencils)
     int vc_kind;          // VcKind
     int step;             // step index: smoothing/anti step, L-BFGS iteration (noise stream)
     float *F_out;         // direct centres: value per job row (may be null)
@@ -77,9 +78,6 @@ bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, c
 hipError_t launch_fill_u8(uint8_t *p, uint8_t v, size_t n, hipStream_t st);
 hipError_t launch_uniform_init(const Dev &D, hipStream_t st);
 hipError_t launch_begin_cycle(const Dev &D, hipStream_t st);
-// Zero the counts of the lists in `mask` of the problems pids[0 .. np)
-// (device array), or of every problem when pids is null.
-hipError_t launch_reset_counts(const Dev &D, int mask, hipStream_t st, const int *pids = nullptr, int np = 0);
 // Stream compaction of the list `src` by D.flag: for each problem, position j
 // of src's segment (j < its count) with flag[j] == v is appended to list
 // dst[v - 1] (v = 1, 2; -1: none); positions with flag == 3 are counted into
@@ -93,11 +91,14 @@ hipError_t launch_compact(const Dev &D, int src, int dst1, int dst2, bool count_
 hipError_t launch_build_unfrozen(const Dev &D, hipStream_t st);
 // Iteration t of the L-BFGS loop for the samples on list `list_in` (all
 // active samples at t = 1, the previous iteration's steppers after), over the
-// list positions [g0, g0 + n) of a set of whole problems, all with
-// d <= 16 cpl; D.flag of a position is set to 1 when its sample was given a
-// direction, else 0.
-hipError_t launch_lbfgs_step(const Dev &D, int t, int cpl, int list_in, int g0, int n, hipStream_t st);
-hipError_t launch_stick(const Dev &D, hipStream_t st);
+// list positions [g0, g0 + n) of a set of whole problems pids[0 .. np), all
+// with d <= 16 cpl; D.flag of a position is set to 1 when its sample was given
+// a direction, else 0.  in_place: list_in is the active list at every t, and
+// the steppers are the samples with a search result.  The counts of the lists
+// in reset_mask (list_in not among them) are zeroed.
+hipError_t launch_lbfgs_step(const Dev &D, int t, int cpl, int list_in, bool in_place, int reset_mask, const int *pids,
+                             int np, int g0, int n, hipStream_t st);
+hipError_t launch_stick(const Dev &D, bool any_noise, hipStream_t st);
 hipError_t launch_dedup(const Dev &D, hipStream_t st);
 hipError_t launch_reseed(const Dev &D, hipStream_t st);
 hipError_t launch_sigma(const Dev &D, hipStream_t st);
