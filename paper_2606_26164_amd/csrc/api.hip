@@ -1272,6 +1272,7 @@ static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, int K
         a.G_out = G_dev;
         a.max_tiles = tiles;
         a.dsplit = direct_split(DP, family, K, tiles);
+        if (DP == kAluDP) return launch_alu_direct(a, d, family, K, G_dev != nullptr, st);
         return launch_eval(a, DP, family, kDirect, false, G_dev != nullptr, st);
     }
     if (f_dev) {
@@ -1279,7 +1280,9 @@ static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, int K
         a.G_out = nullptr;
         a.max_tiles = tiles;
         a.dsplit = direct_split(DP, family, K, tiles);
-        if ((e = launch_eval(a, DP, family, kDirect, false, false, st)) != hipSuccess) return e;
+        e = DP == kAluDP ? launch_alu_direct(a, d, family, K, false, st)
+                         : launch_eval(a, DP, family, kDirect, false, false, st);
+        if (e != hipSuccess) return e;
     }
     if (G_dev) {
         a.F_out = nullptr;

@@ -1514,6 +1514,165 @@ __global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a)
 }
 
 // ---------------------------------------------------------------------------
+// Values and gradients of a small mixture (d <= 8) on caller memory: one point
+// per lane as in the tiles, without their lists, problems and staging.  The
+// component records go through LDS, kAluChunk at a time, and are read as
+// broadcasts (through scalar loads, which cannot be kept in flight, a wave
+// alone on its SIMD took 810 cycles a component of width 8, so 680).
+// SPLIT > 1: the waves of a workgroup share 64 points, each taking every
+// SPLIT-th component, and merge their states through LDS.
+//
+// What bounds it: with waves enough the vector unit, about 100 instructions a
+// component of width 8 at 4 cycles each (two waves' instructions pair up only
+// where their registers allow it; 300000 points, K = 40: 50 us as tiles, 40
+// here); with few points one pass over the components, which the split
+// shortens (16384 points, K = 40: 19.5 us as tiles, 16 unsplit, 7 split).  Two
+// points per lane were slower at every size (300000 points: 50 us).
+// ---------------------------------------------------------------------------
+constexpr int kAluBlock = 256, kAluChunk = 64;
+template <int FAM, bool GRAD, int W, int SPLIT>
+__global__ __launch_bounds__(kAluBlock) void alu_direct_kernel(EvalArgs a) {
+    constexpr int T = W * (W + 1) / 2, R = alu_record(W), kWaves = kAluBlock / kWave;
+    static_assert(SPLIT == 1 || SPLIT == kWaves, "all waves of a workgroup share its points, or none");
+    __shared__ f32x4 s_rec[kAluChunk * (R / 4)];
+    const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const ProblemDesc &pd = a.D.pd[a.cls[0]];
+    const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
+    const float nu = pd.nu, nupd = pd.nu_plus_d, inv_nu = 1.0f / nu;
+    const int i = (SPLIT > 1 ? blockIdx.x : blockIdx.x * kWaves + wv) * kWave + lane;
+    const bool in = i < a.ext_n;
+    float xr[W], ga[GRAD ? W : 1], m = -INFINITY, sm = 0.0f;
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+        xr[c] = (in && c < d) ? as_global(a.X)[(size_t)i * d + c] : 0.0f;
+        if constexpr (GRAD) ga[c] = 0.0f;
+    }
+    for (int k0 = 0; k0 < K; k0 += kAluChunk) {
+        const int n = min(kAluChunk, K - k0);
+        if (k0) __syncthreads();
+        for (int e = threadIdx.x; e < n * (R / 4); e += kAluBlock)
+            s_rec[e] = reinterpret_cast<const gf32x4 *>(as_global(pd.Pfrag) + (size_t)k0 * R)[e];
+        __syncthreads();
+        for (int k = SPLIT == 1 ? 0 : wv; k < n; k += SPLIT) {
+            float rec[R], dl[W], u[W], q = 0.0f;
+#pragma unroll
+            for (int e = 0; e < R / 4; ++e) {
+                const f32x4 v = s_rec[k * (R / 4) + e];
+                rec[4 * e] = v[0]; rec[4 * e + 1] = v[1]; rec[4 * e + 2] = v[2]; rec[4 * e + 3] = v[3];
+            }
+#pragma unroll
+            for (int c = 0; c < W; ++c) dl[c] = xr[c] - rec[T + c];
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                float acc = 0.0f;
+#pragma unroll
+                for (int j = 0; j < W; ++j) {
+                    const int lo = c < j ? c : j, hi = c < j ? j : c;
+                    acc = fmaf(rec[lo * W - lo * (lo - 1) / 2 + (hi - lo)], dl[j], acc);
+                }
+                u[c] = acc;
+                q = fmaf(dl[c], acc, q);
+            }
+            float l2, w = 1.0f;
+            if constexpr (FAM == 0) {
+                l2 = rec[T + W] - q * (0.5f * kLog2e);
+            } else {
+                l2 = rec[T + W] - (0.5f * nupd) * student_log2(q, inv_nu);
+                w = nupd * __builtin_amdgcn_rcpf(nu + q);
+            }
+            const bool moved = l2 > m + kLseSlack;
+            if (__any(moved)) {
+                const float mnew = moved ? l2 : m;
+                const float sc = moved ? __builtin_amdgcn_exp2f(m - mnew) : 1.0f;
+                sm *= sc;
+                if constexpr (GRAD)
+#pragma unroll
+                    for (int c = 0; c < W; ++c) ga[c] *= sc;
+                m = mnew;
+            }
+            const float pk = __builtin_amdgcn_exp2f(l2 - m);
+            sm += pk;
+            if constexpr (GRAD) {
+                const float pw = pk * w;
+#pragma unroll
+                for (int c = 0; c < W; ++c) ga[c] = fmaf(pw, u[c], ga[c]);
+            }
+        }
+    }
+    if constexpr (SPLIT > 1) {
+        // merged as split tiles are: scaled to the largest reference, added in
+        // wave order
+        __shared__ float s_m[SPLIT][kWave], s_s[SPLIT][kWave], s_g[GRAD ? SPLIT * W : 1][kWave];
+        s_m[wv][lane] = m;
+        s_s[wv][lane] = sm;
+        if constexpr (GRAD)
+#pragma unroll
+            for (int c = 0; c < W; ++c) s_g[wv * W + c][lane] = ga[c];
+        __syncthreads();
+        if (wv != 0) return;
+        m = -INFINITY;
+        sm = 0.0f;
+        float av[SPLIT];
+#pragma unroll
+        for (int v = 0; v < SPLIT; ++v) m = fmaxf(m, s_m[v][lane]);
+#pragma unroll
+        for (int v = 0; v < SPLIT; ++v) {
+            const float mv = s_m[v][lane], sv = s_s[v][lane];
+            av[v] = (mv == -INFINITY && sv == 0.0f) ? 0.0f : __builtin_amdgcn_exp2f(mv - m);
+            sm = fmaf(sv, av[v], sm);
+        }
+        if constexpr (GRAD)
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                float g = 0.0f;
+#pragma unroll
+                for (int v = 0; v < SPLIT; ++v) g = fmaf(s_g[v * W + c][lane], av[v], g);
+                ga[c] = g;
+            }
+    }
+    if (!in) return;
+    if (a.F_out) a.F_out[i] = (m + __log2f(sm)) * kLn2;
+    if constexpr (GRAD) {
+        const float inv = -1.0f / sm;
+#pragma unroll
+        for (int c = 0; c < W; ++c)
+            if (c < d) a.G_out[(size_t)i * d + c] = ga[c] * inv;
+    }
+}
+
+// Shared points while that shortens the pass: with 32 components or more at any
+// size (its many small workgroups also fill the last round more evenly: 300000
+// points of width 8, K = 128: 112 us against 114), with 8 or more up to 65536
+// points (K = 16: 8.7 against 9.8 us there, 13.3 against 12.6 at 131072).
+template <int FAM, bool GRAD, int W>
+static hipError_t alu_direct_width(const EvalArgs &a, int K, hipStream_t st) {
+    const long groups = (a.ext_n + kWave - 1) / kWave;
+    constexpr int kWaves = kAluBlock / kWave;
+    const dim3 b(kAluBlock), each((unsigned)((groups + kWaves - 1) / kWaves)), shared((unsigned)groups);
+    if (K >= 32 || (K >= 8 && groups <= 1024))
+        hipLaunchKernelGGL((alu_direct_kernel<FAM, GRAD, W, kWaves>), shared, b, 0, st, a);
+    else
+        hipLaunchKernelGGL((alu_direct_kernel<FAM, GRAD, W, 1>), each, b, 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool grad, hipStream_t st) {
+    if (a.ext_n <= 0) return hipSuccess;
+#define CHISAO_ALU(F, G)                                                  \
+    switch (alu_width(d)) {                                               \
+        case 2: return alu_direct_width<F, G, 2>(a, K, st);               \
+        case 4: return alu_direct_width<F, G, 4>(a, K, st);               \
+        default: return alu_direct_width<F, G, 8>(a, K, st);              \
+    }
+    if (family == 0) {
+        if (grad) CHISAO_ALU(0, true) else CHISAO_ALU(0, false)
+    } else {
+        if (grad) CHISAO_ALU(1, true) else CHISAO_ALU(1, false)
+    }
+#undef CHISAO_ALU
+}
+
+// ---------------------------------------------------------------------------
 // Dispatch
 // ---------------------------------------------------------------------------
 template <int DP, int FAM, bool H16>

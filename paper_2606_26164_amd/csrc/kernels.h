@@ -50,6 +50,10 @@ struct EvalArgs {
 constexpr int kSplitHalf = 8, kSplitFull = 4;
 int direct_split(int DP, int family, int K, long tiles);
 
+// Values (F_out, may be null) and gradients (G_out, with grad) of one mixture
+// with d <= 8 at the ext_n dense rows of X: caller memory only.
+hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool grad, hipStream_t st);
+
 // center: kDirect / kTrial / kProbe; fd: stencil around each centre;
 // grad: accumulate the adjoint gradient.
 hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool fd, bool grad, hipStream_t st);

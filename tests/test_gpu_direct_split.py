@@ -37,7 +37,16 @@ def test_either_side_of_each_size(d, K, fam, B):
     _check(prob, base[at[rows]], f[rows], G[rows])
 
 
-@pytest.mark.parametrize("d", [16, 40])
+@pytest.mark.parametrize("d,K,fam", [(1, 8, W.GAUSS), (2, 7, W.STUDENT_T), (3, 31, W.GAUSS), (4, 32, W.STUDENT_T),
+                                     (5, 65, W.GAUSS), (8, 130, W.GAUSS)])
+@pytest.mark.parametrize("B", [1, 63, 65, 65536, 65537])
+def test_small_mixtures(d, K, fam, B):
+    """Either side of the sizes at which four waves share 64 points, with more
+    components than one staged chunk among them."""
+    test_either_side_of_each_size(d, K, fam, B)
+
+
+@pytest.mark.parametrize("d", [3, 16, 40])
 def test_a_nan_stays_in_its_row(d):
     prob = W.mixture_problem(21, d, 3, 5.0, lam_range=(0.1, 1.0))
     X = _points(prob, 40, 2)
@@ -53,8 +62,8 @@ def test_a_nan_stays_in_its_row(d):
 def test_handle_free_evaluation_takes_the_same_path():
     from paper_2606_26164_amd.api import eval_static
 
-    prob = W.mixture_problem(22, 40, 12, 5.0, lam_range=(0.1, 1.0))
-    for B in (33, 5000, 20000):
+    for d, B in ((40, 33), (40, 5000), (40, 20000), (6, 100), (6, 70000)):
+        prob = W.mixture_problem(22, d, 12, 5.0, lam_range=(0.1, 1.0))
         X = torch.from_numpy(_points(prob, B, 4)).cuda()
         with _opt(prob) as opt:
             f, G = opt.eval(X)
