@@ -438,23 +438,37 @@ int direct_split(int DP, int family, int K, long tiles) {
 // in wave order, then runs the epilogue.  Line-search launches are small (a
 // few thousand points), so their time is the latency of one tile's pass over
 // all K components; splitting the components cuts that latency.
-template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT, bool H16>
-__global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2))) void eval_kernel(EvalArgs a) {
+//
+// SHARE (large two-part launches): four waves take 32 points each of a
+// 128-point tile and go through the components together.  A component's
+// fragments are brought to LDS once for the four, by direct loads one component
+// ahead, instead of through the vector cache four times (16 KB each at d = 64, for about
+// 2000 cycles of work): 262144 points, K = 128, values and gradients 905 -> 867
+// us, values 859 -> 808; a cycle of 65536 samples 19.9 -> 19.0 ms.
+constexpr int kShareWaves = 4;
+template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT, bool H16, bool SHARE = false>
+__global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((amdgpu_waves_per_eu(2))) void eval_kernel(EvalArgs a) {
     constexpr int KS = DP / 4;
     constexpr int MB = DP / 16;
     constexpr bool CLOSED = FAM >= kFamClosed;
     // small mixtures: one lane per point on the VALU, 64 points per tile
     constexpr bool ALU = !CLOSED && DP == kAluDP;
-    constexpr int PPW = ALU ? kWave : kTilePts;
+    constexpr int PPW = ALU ? kWave : (SHARE ? kShareWaves * kTilePts : kTilePts);
     constexpr int LD = DP + 1;  // padded row: conflict-free column reads
+    static_assert(!SHARE || (DP == 64 && H16 && SPLIT == 1 && !HT && !FD && CENTER != kTrial), "shared components: large launches");
+    // (SHARE) a component in LDS: fragments, scaled centre
+    constexpr int kCompF = SHARE ? DP * DP + DP : 0;
     // split direct evaluations: every wave's partial state goes through LDS and
     // all waves merge; split line-search tiles: waves 1.. hand theirs to the first
     constexpr bool DSPLIT = CENTER == kDirect && SPLIT > 1;
     constexpr int NP = SPLIT == 1 ? 1 : (DSPLIT ? SPLIT : SPLIT - 1), NBP = HT ? 1 : NB;
     __shared__ float s_pm[NP][NBP][kWave], s_ps[NP][NBP][kWave];             // partial max / sum
     __shared__ float s_pg[(SPLIT > 1 && GRAD) ? NP * NBP * KS : 1][kWave];  // partial gradient sums
-    __shared__ float s_pts[PPW * LD];
-    __shared__ float s_g[GRAD ? PPW * LD : 1];
+    // (SHARE) the points, then two components in turn, then the gradients
+    constexpr int kPtsF = PPW * LD > 2 * kCompF ? PPW * LD : 2 * kCompF;
+    __shared__ __align__(16) float s_pts[kPtsF];
+    __shared__ float s_grad[GRAD && !SHARE ? PPW * LD : 1];
+    float *s_g = SHARE ? s_pts : s_grad;
     __shared__ float s_f[PPW];
     __shared__ float s_den[PPW];
     __shared__ int s_s[PPW];    // sample (or caller row) per point, -1 when the lane is idle
@@ -486,6 +500,9 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
     const Dev &D = a.D;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     const bool lead = SPLIT == 1 || wv == 0;
+    const int tl = SHARE ? (int)threadIdx.x : lane;      // one thread per point of the tile
+    const int wp = SHARE ? wv * kTilePts : 0;            // the wave's first point
+    constexpr int kTl = SHARE ? kShareWaves * kWave : kWave;
     const int g = lane >> 4, n = lane & 15;
     const bool ext = a.ext_n >= 0;
     // Tile prefix over the problems of the class.  Line-search launches are
@@ -595,8 +612,8 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
         const int xs = a.x_stride;
         const int *lst = (!ext && a.list_id >= 0) ? list_ptr(D, a.list_id, pd.s0) : nullptr;
         // ---- point metadata ------------------------------------------------
-        if (lead && lane < PPW) {
-            const int pt = lane;
+        if (lead && tl < PPW) {
+            const int pt = tl;
             int job, v;
             bool valid;
             if (V <= ppw) {
@@ -885,7 +902,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             float cn[H16 ? NB : 1], kqn[H16 ? NB : 1], kgn[H16 ? NB : 1];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                const float *row = s_pts + (nb * 16 + n) * LD;
+                const float *row = s_pts + (wp + nb * 16 + n) * LD;
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) xB[nb][ks] = row[lane_coord(ks, g)];
             }
@@ -944,6 +961,37 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             const __amdgpu_buffer_rsrc_t rs_mu = table_rsrc(H16 ? pd.muB2 : pd.muB, (uint32_t)Kc * DP * 4u);
             const __amdgpu_buffer_rsrc_t rs_lc = table_rsrc(pd.logc2, (uint32_t)Kc * 4u);
             const int mu_lane = g * KS * 4;
+            // (SHARE) component k into half b of s_pts, by every thread; waited
+            // for by the next barrier
+            [[maybe_unused]] auto fetch = [&](int k, int b) {
+                typedef const void __attribute__((address_space(1))) * gptr;
+                typedef void __attribute__((address_space(3))) * lptr;
+                const float *src = pd.Pfrag2 + (size_t)k * DP * DP;
+                float *dst = s_pts + b * kCompF;
+#pragma unroll
+                for (int i = 0; i < DP * DP / (4 * kShareWaves * kWave); ++i)
+                    __builtin_amdgcn_global_load_lds((gptr)(src + 4 * (i * kShareWaves * kWave + threadIdx.x)),
+                                                     (lptr)(dst + 4 * (i * kShareWaves + wv) * kWave), 16, 0, 0);
+                if (threadIdx.x < DP / 4)
+                    __builtin_amdgcn_global_load_lds((gptr)(pd.muB2 + (size_t)k * DP + 4 * threadIdx.x),
+                                                     (lptr)(dst + DP * DP), 16, 0, 0);
+            };
+            [[maybe_unused]] auto load_shared = [&](int b, Regs &r) {
+                if constexpr (SHARE) {
+                    const float *src = s_pts + b * kCompF;
+#pragma unroll
+                    for (int i = 0; i < 2 * r.S * MB; ++i) {
+                        const int part = i % 2, blk = i / 2;
+                        r.pa[part][blk / MB][blk % MB] = *reinterpret_cast<const f16x8 *>(
+                            src + 4 * ((part * r.S * MB + blk) * kWave + lane));
+                    }
+#pragma unroll
+                    for (int i = 0; i < KS; i += 4) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + DP * DP + g * KS + i);
+                        r.muB[i] = v[0]; r.muB[i + 1] = v[1]; r.muB[i + 2] = v[2]; r.muB[i + 3] = v[3];
+                    }
+                }
+            };
             [[maybe_unused]] const int pf_lane = lane * MB * 4;
             float neg1 = -1.0f;
             if constexpr (H16) asm("" : "+s"(neg1));
@@ -1138,7 +1186,29 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
             const int K = __builtin_amdgcn_readfirstlane(pd.K);
             const int wvu = __builtin_amdgcn_readfirstlane(wv);
             const int kb = SPLIT == 1 ? 0 : (wvu * K) / SPLIT, ke = SPLIT == 1 ? K : ((wvu + 1) * K) / SPLIT;
-            if constexpr (DP < 64) {
+            if constexpr (SHARE) {
+                auto loop = [&](auto four) {
+                    auto lc = [&](int k) {
+                        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs_lc, 0, k * 4, 0));
+                    };
+                    __syncthreads();  // the points are in registers
+                    float lc_next = lc(0);
+                    fetch(0, 0);
+                    __syncthreads();
+                    for (int k = 0; k < K; ++k) {
+                        ra.lc2 = lc_next;
+                        const int kn = min(k + 1, K - 1);
+                        lc_next = lc(kn);
+                        fetch(kn, (k + 1) & 1);
+                        load_shared(k & 1, ra);
+                        step(ra, AllBlocks{}, four);
+                        __syncthreads();
+                    }
+                };
+                if (d <= kTwoPartLowD) loop(std::true_type{});
+                else loop(std::false_type{});
+                own_to_blocks(AllBlocks{});
+            } else if constexpr (DP < 64) {
                 // small components: too little work per component to hide its load
                 // latency behind the other wave, so the next one is loaded into a
                 // second register set while this one is contracted (the set is
@@ -1265,7 +1335,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 if (DSPLIT || !lead || ((HALF || HT) && nb * 16 >= ppw)) break;
-                const int pt = nb * 16 + n;
+                const int pt = wp + nb * 16 + n;
                 float f = (mrun[nb] + __log2f(srun[nb])) * kLn2;
                 if (noisy && g == 0 && s_s[pt] >= 0) f += noise_of(pt);
                 if (g == 0) s_f[pt] = f;
@@ -1285,10 +1355,10 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
         // ---- epilogues -----------------------------------------------------
         const int os = a.out_stride;
         if constexpr (CENTER == kDirect && !FD) {
-            if (lead && lane < PPW && s_s[lane] >= 0 && a.F_out) a.F_out[s_s[lane]] = s_f[lane];
+            if (lead && tl < PPW && s_s[tl] >= 0 && a.F_out) a.F_out[s_s[tl]] = s_f[tl];
             if constexpr (GRAD) {
                 if (a.G_out)
-                    for (int e = threadIdx.x; e < PPW * d; e += kWave * SPLIT) {
+                    for (int e = threadIdx.x; e < PPW * d; e += blockDim.x) {
                         const int pt = e / d, c = e % d, s = s_s[pt];
                         if (s >= 0) a.G_out[(size_t)s * os + c] = s_g[pt * LD + c];
                     }
@@ -1306,7 +1376,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
         } else if constexpr (CENTER == kProbe) {
             // mean over the job's probes, summed in probe order
             const float invM = 1.0f / (float)Vc;
-            for (int e = lead ? lane : jpw * d; e < jpw * d; e += kWave) {
+            for (int e = lead ? tl : jpw * d; e < jpw * d; e += kTl) {
                 const int j = e / d, c = e % d, p0 = j * Vc, s = s_s[p0];
                 if (s >= 0) {
                     float acc = 0.0f;
@@ -1692,6 +1762,15 @@ static hipError_t dispatch_modes(const EvalArgs &a, int center, bool fd, bool gr
 #define CHISAO_GO_DSPLIT(G, N, HALF) \
     hipLaunchKernelGGL((eval_kernel<DP, FAM, G, kDirect, false, N, HALF, H16>), grid, dim3(kWave * N), 0, st, a)
     constexpr bool kHalfOk = FAM < kFamClosed && DP != kAluDP;  // tiles of two MFMA column blocks
+    if constexpr (H16 && DP == 64) {
+        if (a.share) {
+            const dim3 b4(kShareWaves * kWave);
+            if (center == kProbe) hipLaunchKernelGGL((eval_kernel<DP, FAM, true, kProbe, false, 1, false, true, true>), grid, b4, 0, st, a);
+            else if (grad) hipLaunchKernelGGL((eval_kernel<DP, FAM, true, kDirect, false, 1, false, true, true>), grid, b4, 0, st, a);
+            else hipLaunchKernelGGL((eval_kernel<DP, FAM, false, kDirect, false, 1, false, true, true>), grid, b4, 0, st, a);
+            return hipGetLastError();
+        }
+    }
     if (center == kDirect) {
         if (fd) CHISAO_GO(kDirect, false, true);
         else if (kHalfOk && a.dsplit) {
@@ -1777,7 +1856,17 @@ static hipError_t dispatch_family(const EvalArgs &a, int fam, int center, bool f
     return dispatch_modes<DP, kFamClosed, false>(a, center, fd, grad, grid, st);
 }
 
-hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool fd, bool grad, hipStream_t st) {
+// 128-point tiles with shared components: at width 64, from the 2048 tiles of
+// 32 points on that make 512 workgroups, two for every CU (at 1024 tiles it is
+// 185 us against 154, K = 128; at 2048 252 against 264).  At width 32 a
+// component is 4 KB and not worth the barrier: 182 us against 159 (262144
+// points, K = 48).
+static bool share_components(const EvalArgs &a, int DP, int center, bool fd) {
+    if (!a.split || DP != 64 || fd || center == kTrial || a.dsplit) return false;
+    return a.max_tiles >= 2048 && !(center == kDirect && a.half_tiles);
+}
+
+hipError_t launch_eval(EvalArgs a, int DP, int family, int center, bool fd, bool grad, hipStream_t st) {
     if (a.max_tiles <= 0 || a.n_cls <= 0) return hipSuccess;
     if (a.n_cls > kMaxClass) return hipErrorInvalidValue;
     if (fd && family >= kFamClosed) {
@@ -1791,7 +1880,10 @@ hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool f
     const long cap = a.grid_cap > 0 ? a.grid_cap : 8192;
     // max_tiles counts 32-point tiles; half tiles are twice as many
     const bool halves = a.half_tiles || a.dsplit == kSplitHalf;
-    const long tiles = (center == kDirect && !fd && halves) ? 2 * a.max_tiles : a.max_tiles;
+    a.share = share_components(a, DP, center, fd);
+    // (a tile of each problem may be partly filled)
+    const long tiles = a.share ? a.max_tiles / kShareWaves + a.n_cls
+                               : ((center == kDirect && !fd && halves) ? 2 * a.max_tiles : a.max_tiles);
     long g = tiles < cap ? tiles : cap;
     if (a.order == 1) g = (g + 7) / 8 * 8;  // whole rounds over the XCDs
     const dim3 grid((unsigned)g);

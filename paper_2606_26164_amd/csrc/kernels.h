@@ -41,6 +41,7 @@ struct EvalArgs {
     int half_tiles;       // direct value (+ gradient) launches of matrix-core classes: 16-point tiles
     uint32_t nz_base;     // noise sub-stream base (kind 0); the noise step is `step`
     int dsplit;           // direct value (+ gradient) launches on caller memory: direct_split()
+    int share;            // set by launch_eval: 128-point tiles whose waves share a component's operands
     int split;            // contract in two f16 parts (the problems have those tables)
 };
 
@@ -56,7 +57,7 @@ hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool g
 
 // center: kDirect / kTrial / kProbe; fd: stencil around each centre;
 // grad: accumulate the adjoint gradient.
-hipError_t launch_eval(const EvalArgs &a, int DP, int family, int center, bool fd, bool grad, hipStream_t st);
+hipError_t launch_eval(EvalArgs a, int DP, int family, int center, bool fd, bool grad, hipStream_t st);
 
 // Workgroups of a class's line-search launch that are resident at once on the
 // current GPU (0: no limit applies).  Line-search launches use that many
