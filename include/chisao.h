@@ -119,7 +119,7 @@ typedef struct {
     uint32_t flags;     /* CHISAO_FLAG_* (handle-wide; taken from the first problem of a batch) */
 } chisao_config;
 
-#define CHISAO_FLAG_NO_GRAPH 1u    /* enqueue every cycle's kernels one by one instead of replaying a captured hipGraph */
+#define CHISAO_FLAG_NO_GRAPH 1u    /* enqueue every cycle's kernels one by one, never replaying a captured hipGraph */
 #define CHISAO_FLAG_NO_AUTOTUNE 2u /* keep the default evaluation schedule (linear tile order, 8192 workgroups,
                                       line-search launches included) */
 /* Read per problem: when the problem's starting population is not given, draw
@@ -233,7 +233,8 @@ int chisao_init_batched(chisao_handle *out, int n_problems, const chisao_problem
 
 /* Run n_cycles oscillation cycles (Algorithm 1 body) of every problem.
  * Phases 4-6 are skipped in cycle n_osc.  Work is enqueued asynchronously (by
- * default as one captured hipGraph per cycle); when stats_host is not NULL the
+ * default as one captured hipGraph per cycle where it will be replayed often
+ * enough, kernel by kernel otherwise); when stats_host is not NULL the
  * call synchronizes and fills n_cycles * n_problems entries, cycle-major.
  * Running past n_osc fails with CHISAO_E_STATE and runs nothing. */
 int chisao_cycle(chisao_handle h, int n_cycles, chisao_cycle_stats *stats_host);
@@ -320,7 +321,8 @@ const char *chisao_last_error(void);
  * times CHISAO_TUNE_VARIANTS schedules over the starting population, on a
  * value + adjoint gradient pass (adjoint classes) or a central-difference
  * stencil pass (finite-difference classes): each variant once untimed, then
- * two rounds over the variants, a variant's time its fastest launch.  It
+ * two rounds over the variants, a variant's time its fastest launch (variants
+ * whose launches are the same are timed as one).  It
  * keeps the default (variant 0) unless another is at least 3% faster than the
  * best so far: variant v uses
  * tile order v % 2 (0 linear, 1 XCD-chunked) and a grid of 8192 (v < 2) or

@@ -111,6 +111,7 @@ struct chisao_ctx {
     int *io_flag = nullptr;        // device: first offending row of a box check
     Buffers buf;
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // [0]: cycles before n_osc, [1]: the last cycle
+    int plain_runs[2] = {0, 0};                    // cycles of each kind run kernel by kernel so far
     // profiling: event pairs recorded around launches of each class
     bool prof = false;
     std::vector<hipEvent_t> ev_pool;
@@ -680,23 +681,51 @@ static hipError_t run_eval(chisao_ctx *h, const EvalClass &c, EvalArgs &a, int c
 // Times n launch variants of one pass: every variant once untimed (clocks
 // and caches settle, so the first variant measured is not the coldest), then
 // kTuneRounds rounds over the variants in turn, each launch between its own
-// events; a variant's time is its fastest launch.
+// events; a variant's time is its fastest launch.  The launches of a pass are
+// waited for together.  same_as(v) <= v: the variant whose launch v repeats (it
+// takes that one's time).
 constexpr int kTuneRounds = 2;
-template <class F>
-static hipError_t time_variants(chisao_ctx *h, hipEvent_t e0, hipEvent_t e1, int n, F &&launch, float *ms_out) {
+struct TuneEvents {
+    hipEvent_t e[kTuneRounds][kTuneVariants][2] = {};
+    hipError_t create() {
+        for (auto &r : e)
+            for (auto &v : r)
+                for (hipEvent_t &x : v) {
+                    const hipError_t err = hipEventCreate(&x);
+                    if (err != hipSuccess) return err;
+                }
+        return hipSuccess;
+    }
+    ~TuneEvents() {
+        for (auto &r : e)
+            for (auto &v : r)
+                for (hipEvent_t x : v)
+                    if (x) (void)hipEventDestroy(x);
+    }
+};
+template <class F, class S>
+static hipError_t time_variants(chisao_ctx *h, TuneEvents &ev, int n, F &&launch, S &&same_as, float *ms_out) {
     hipError_t e = hipSuccess;
-    for (int v = 0; v < n && e == hipSuccess; ++v) e = launch(v);
-    for (int v = 0; v < n; ++v) ms_out[v] = 0.0f;
-    for (int r = 0; r < kTuneRounds && e == hipSuccess; ++r)
+    for (int r = -1; r < kTuneRounds; ++r)
         for (int v = 0; v < n && e == hipSuccess; ++v) {
-            e = hipEventRecord(e0, h->stream);
+            if (same_as(v) != v) continue;
+            if (r >= 0) e = hipEventRecord(ev.e[r][v][0], h->stream);
             if (e == hipSuccess) e = launch(v);
-            if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            if (r >= 0 && e == hipSuccess) e = hipEventRecord(ev.e[r][v][1], h->stream);
+        }
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    for (int v = 0; v < n; ++v) ms_out[v] = 0.0f;
+    for (int v = 0; v < n && e == hipSuccess; ++v) {
+        if (same_as(v) != v) {
+            ms_out[v] = ms_out[same_as(v)];
+            continue;
+        }
+        for (int r = 0; r < kTuneRounds && e == hipSuccess; ++r) {
             float ms = 0.0f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+            e = hipEventElapsedTime(&ms, ev.e[r][v][0], ev.e[r][v][1]);
             if (e == hipSuccess && (r == 0 || ms < ms_out[v])) ms_out[v] = ms;
         }
+    }
     return e;
 }
 
@@ -722,13 +751,15 @@ static int pick_variant(const float *ms, int n) {
 // pass would take seconds).  Every point's arithmetic is the same in every
 // schedule and tile size, so results do not depend on the choice.
 static int autotune(chisao_ctx *h) {
-    hipEvent_t e0, e1;
-    HIP_TRY(hipEventCreate(&e0));
-    hipError_t e = hipEventCreate(&e1);
-    if (e != hipSuccess) {
-        (void)hipEventDestroy(e0);
-        return fail(CHISAO_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
-    }
+    TuneEvents ev;
+    hipError_t e = ev.create();
+    if (e != hipSuccess) return fail(CHISAO_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
+    // a launch of no more tiles than the smallest grid is the same under every
+    // grid size: variants 2 and 3 repeat 0 and 1
+    auto same_as = [](long tiles) {
+        return [tiles](int v) { return v >= 2 && tiles <= kTuneCap[v] ? v - 2 : v; };
+    };
+    auto each = [](int v) { return v; };
     for (EvalClass &c : h->eclasses) {
         // the pass the class runs most: value and adjoint gradient, or the
         // central-difference stencils (a value-only pass is far shorter and
@@ -739,11 +770,11 @@ static int autotune(chisao_ctx *h) {
         a.F_out = adj ? h->D.F : nullptr;
         a.G_out = h->D.G;
         a.max_tiles = tile_bound(h, c, kVcOne, fd);
-        e = time_variants(h, e0, e1, kTuneVariants, [&](int v) {
+        e = time_variants(h, ev, kTuneVariants, [&](int v) {
             a.order = kTuneOrder[v];
             a.grid_cap = kTuneCap[v];
             return launch_eval(a, c.DP, c.family, kDirect, fd, adj, h->stream);
-        }, c.tune_ms);
+        }, same_as(a.max_tiles), c.tune_ms);
         if (e != hipSuccess) break;
         const int best_v = pick_variant(c.tune_ms, kTuneVariants);
         c.order = kTuneOrder[best_v];
@@ -756,10 +787,10 @@ static int autotune(chisao_ctx *h) {
             float ms2[2];
             a.order = c.order;
             a.grid_cap = c.grid_cap;
-            e = time_variants(h, e0, e1, 2, [&](int v) {
+            e = time_variants(h, ev, 2, [&](int v) {
                 a.half_tiles = v;
                 return launch_eval(a, c.DP, c.family, kDirect, false, true, h->stream);
-            }, ms2);
+            }, each, ms2);
             if (e != hipSuccess) break;
             c.tune_full_ms = ms2[0];
             c.tune_half_ms = ms2[1];
@@ -771,18 +802,16 @@ static int autotune(chisao_ctx *h) {
         EvalArgs b = base_args(h, c);
         b.vc_kind = kVcProbes;
         b.max_tiles = tile_bound(h, c, kVcProbes, false);
-        e = time_variants(h, e0, e1, kTuneVariants, [&](int v) {
+        e = time_variants(h, ev, kTuneVariants, [&](int v) {
             b.order = kTuneOrder[v];
             b.grid_cap = kTuneCap[v];
             return launch_eval(b, c.DP, c.family, kProbe, false, true, h->stream);
-        }, c.tune_probe_ms);
+        }, same_as(b.max_tiles), c.tune_probe_ms);
         if (e != hipSuccess) break;
         const int pv = pick_variant(c.tune_probe_ms, kTuneVariants);
         c.p_order = kTuneOrder[pv];
         c.p_grid_cap = kTuneCap[pv];
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     if (e != hipSuccess) return fail(CHISAO_E_DEVICE, "autotuning launch failed: %s", hipGetErrorString(e));
     return CHISAO_OK;
 }
@@ -1044,6 +1073,19 @@ extern "C" int chisao_run_phases(chisao_handle h, uint32_t phase_mask) {
     return CHISAO_OK;
 }
 
+// A cycle is captured when enough replays are in sight to pay for it: capture,
+// instantiation and destruction cost about 6 us a launch of the cycle, and a
+// replay saves 2 us a launch of host time at most (d = 6, N = 256: 0.35 ms
+// against 0.2 a cycle; a batch of 16 problems, whose cycles are as long as
+// their kernels either way: 3 ms for nothing).  In sight: the cycles of the
+// kind that are left (one last cycle); and, for a handle that is set back, as
+// many as it has run so already.
+constexpr int kGraphMinCycles = 4;
+static bool worth_capturing(const chisao_ctx *h, bool last) {
+    const int left = last ? 1 : h->D.n_osc - 1 - h->k_host;
+    return left >= kGraphMinCycles || h->plain_runs[last ? 1 : 0] >= kGraphMinCycles;
+}
+
 extern "C" int chisao_cycle(chisao_handle h, int n_cycles, chisao_cycle_stats *stats_host) {
     if (!h) return fail(CHISAO_E_INVAL, "null handle");
     if (n_cycles < 0) return fail(CHISAO_E_INVAL, "negative cycle count");
@@ -1055,8 +1097,8 @@ extern "C" int chisao_cycle(chisao_handle h, int n_cycles, chisao_cycle_stats *s
     const bool graphs = !(h->flags & CHISAO_FLAG_NO_GRAPH) && !h->prof;
     for (int i = 0; i < n_cycles; ++i) {
         const bool last = (h->k_host + 1 == h->D.n_osc);
-        if (graphs) {
-            hipGraphExec_t &g = h->graph[last ? 1 : 0];
+        hipGraphExec_t &g = h->graph[last ? 1 : 0];
+        if (graphs && (g || worth_capturing(h, last))) {
             if (!g) {
                 int rc = capture_cycle(h, last, &g);
                 if (rc) return rc;
@@ -1065,6 +1107,8 @@ extern "C" int chisao_cycle(chisao_handle h, int n_cycles, chisao_cycle_stats *s
         } else {
             h->cur = h->stream;
             HIP_TRY(enqueue_cycle(h, last));
+            int &runs = h->plain_runs[last ? 1 : 0];
+            runs = std::min(runs + 1, kGraphMinCycles);
         }
         h->k_host += 1;
     }

@@ -442,9 +442,9 @@ int direct_split(int DP, int family, int K, long tiles) {
 // SHARE (large two-part launches): four waves take 32 points each of a
 // 128-point tile and go through the components together.  A component's
 // fragments are brought to LDS once for the four, by direct loads one component
-// ahead, instead of through the vector cache four times (16 KB each at d = 64, for about
-// 2000 cycles of work): 262144 points, K = 128, values and gradients 905 -> 867
-// us, values 859 -> 808; a cycle of 65536 samples 19.9 -> 19.0 ms.
+// ahead, instead of through the vector cache four times (16 KB each for
+// about 2000 cycles of work): 262144 points, K = 128, values and gradients 905
+// -> 867 us, values 859 -> 808; a cycle of 65536 samples 20.2 -> 19.0 ms.
 constexpr int kShareWaves = 4;
 template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT, bool H16, bool SHARE = false>
 __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((amdgpu_waves_per_eu(2))) void eval_kernel(EvalArgs a) {
