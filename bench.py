@@ -15,8 +15,9 @@ ratio between the two are reported beside it.  The timed cycles run as the
 library runs them by default, one captured hipGraph replayed per cycle; a few
 further cycles are then launched one by one with HIP events around every
 launch, which give the roofline position of the dominant kernel (priced
-against the published and the measured peaks), the kernel time breakdown and
-the active share of the sample-iterations.  Also reported: the
+against the published peak of the matrix instructions it runs on, and the
+measured one where that is float32), the kernel time breakdown and the active
+share of the sample-iterations.  Also reported: the
 other workloads' throughput (d=16 finite differences, the 64-problem batch,
 the noisy Student-t mixture, a closed form), the mode recall of a full run
 against the FP64 reference, and the FP64 CPU oracle's throughput on bounded
@@ -33,6 +34,7 @@ import time
 
 METRIC = "sample-iterations/s at d=64,N=65536 (adjoint vs FD grad); mode recall vs oracle"
 PEAK_FP32_MFMA_TFLOPS = 157.3
+PEAK_F16_MFMA_TFLOPS = 2516.6  # dense
 PEAK_FP32_VECTOR_TFLOPS = 157.3  # 256 CUs x 4 SIMDs x 16 lanes x 2 (FMA) x 2 (packed) x 2.4 GHz
 PEAK_HBM_GBS = 8000.0
 ALU_DP = 8  # mixtures with d <= 8 are evaluated on the VALU, one point per lane
@@ -47,6 +49,27 @@ def executed_width(d: int) -> int:
     """Coordinates a point's arithmetic runs over: 2, 4 or 8 on the VALU path,
     the padded tile width otherwise."""
     return (2 if d <= 2 else (4 if d <= 4 else 8)) if d <= ALU_DP else padded_width(d)
+
+
+def two_part_products(prob, cfg) -> int:
+    """f16 matrix products per component of a population's contraction: 0 where
+    it runs in float32 (d <= 16, closed forms, or no more than 2048 samples),
+    else 3, and 4 up to d = 48 (every mixture here meets the rule on the box's
+    span).  The operands are two f16 parts each; the sums are float32."""
+    if prob.family > 1 or prob.d < 17 or cfg.N < 2049:
+        return 0
+    return 4 if prob.d <= 48 else 3
+
+
+def matrix_seconds_per_point(prob, cfg) -> float:
+    """Time of one evaluation's arithmetic at the published peaks: the executed
+    products at the f16 matrix peak in two parts, the algorithmic flops at the
+    float32 matrix (or vector) peak otherwise."""
+    n = two_part_products(prob, cfg)
+    if n:
+        return prob.K * n * 2 * padded_width(prob.d) ** 2 / (PEAK_F16_MFMA_TFLOPS * 1e12)
+    return eval_flops_per_point(prob.d, prob.K) / (PEAK_FP32_MFMA_TFLOPS * 1e12)
+
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 PROFILES = os.path.join(HERE, "profiles")
@@ -203,22 +226,33 @@ def active_fraction(items, r):
 def eval_roofline(items, r, peaks, dominant_only=True):
     """Roofline of the evaluation launches over the profiled cycles.  With one
     problem the dominant launch kind (by time); otherwise all evaluation
-    launches of the handle, with the problems' own evaluation counts."""
+    launches of the handle, with the problems' own evaluation counts.
+    `achieved` counts algorithmic flops; `peak` is the rate of those flops if
+    the arithmetic ran at the published peaks, so `frac` is the share of the
+    launches' time that the arithmetic needs at these peaks."""
     prof = r["profile"]
     if dominant_only:
-        prob = items[0][0]
+        prob, cfg, _ = items[0]
         dom = max((k for k in prof if k.startswith("eval") and prof[k]["ms"] > 0), key=lambda k: prof[k]["ms"])
         p = prof[dom]
         fpp = eval_flops_per_point(prob.d, prob.K)
         flops, ms, launches = p["points"] * fpp, p["ms"], p["launches"]
+        floor_s = p["points"] * matrix_seconds_per_point(prob, cfg)
         kernel, traffic = f"eval_kernel ({dom})", (measured_traffic(dom) if prob.d == 64 and prob.K == 128 else None)
         extra = dict(flops_per_point=fpp, points=p["points"])
+        n = two_part_products(prob, cfg)
+        if n:
+            extra.update(f16_products=n, achieved_f16=floor_s * PEAK_F16_MFMA_TFLOPS / (ms * 1e-3),
+                         peak_f16=PEAK_F16_MFMA_TFLOPS,
+                         note="contraction in two f16 parts per operand, float32 sums: achieved and peak count the "
+                              "algorithmic flops, achieved_f16 and peak_f16 the matrix products executed")
     else:
-        flops = padded = 0
+        flops = padded = floor_s = 0
         for cyc in r["stats"]:
-            for (prob, _, _), s in zip(items, cyc):
+            for (prob, cfg, _), s in zip(items, cyc):
                 flops += s["evals"] * eval_flops_per_point(prob.d, prob.K)
                 padded += s["evals"] * eval_flops_per_point(executed_width(prob.d), prob.K)
+                floor_s += s["evals"] * matrix_seconds_per_point(prob, cfg)
         ev = [k for k in prof if k.startswith("eval")]
         ms = sum(prof[k]["ms"] for k in ev)
         launches = sum(prof[k]["launches"] for k in ev)
@@ -226,14 +260,14 @@ def eval_roofline(items, r, peaks, dominant_only=True):
         extra = dict(achieved_padded=padded / (ms * 1e-3) / 1e12,
                      note="achieved counts each problem's own d; achieved_padded the work at the width the "
                           "kernel executes (tiles padded to 16, 32 or 64; 2, 4 or 8 on the VALU path)")
-    achieved = flops / (ms * 1e-3) / 1e12
-    # mixtures with d <= 8 run on the VALU, the rest on the FP32 matrix cores
+    achieved, peak = flops / (ms * 1e-3) / 1e12, flops / floor_s / 1e12
+    # mixtures with d <= 8 run on the VALU, the rest on the matrix cores
     alu = all(padded_width(prob.d) == ALU_DP for prob, _, _ in items)
-    peak = PEAK_FP32_VECTOR_TFLOPS if alu else PEAK_FP32_MFMA_TFLOPS
+    f32 = not any(two_part_products(prob, cfg) for prob, cfg, _ in items)
     out = dict(bound="alu" if alu else "mfma", achieved=achieved, peak=peak, unit="TFLOP/s",
                frac=achieved / peak, traffic=traffic, traffic_unit="bytes per launch",
                kernel=kernel, launches=launches, avg_launch_ms=ms / max(launches, 1))
-    if peaks and not alu:
+    if peaks and f32 and not alu:
         out.update(peak_measured=peaks["fp32_mfma_tflops"], frac_measured=achieved / peaks["fp32_mfma_tflops"])
     if alu:
         # the vector peak counts packed FP32 (two lanes' worth per instruction);
@@ -244,22 +278,23 @@ def eval_roofline(items, r, peaks, dominant_only=True):
     return out
 
 
-def cycle_roofline(prob, r, peaks):
+def cycle_roofline(prob, cfg, r, peaks):
     """Every objective evaluation of the profiled cycles (their evaluation
     counts times the algorithmic flops per point) over those cycles' wall time
-    (launched one by one with events, a little slower than graph replay)."""
+    (launched one by one with events, a little slower than graph replay);
+    `peak` as in eval_roofline."""
     n = r["profile_steps"]
     if n <= 0 or r["profile_seconds"] <= 0:
         return None
     evals = sum(s["evals"] for cyc in r["stats"] for s in cyc)
-    flops = evals * eval_flops_per_point(prob.d, prob.K)
-    achieved = flops / r["profile_seconds"] / 1e12
-    out = dict(bound="mfma", achieved=achieved, peak=PEAK_FP32_MFMA_TFLOPS, unit="TFLOP/s",
-               frac=achieved / PEAK_FP32_MFMA_TFLOPS, evaluations_per_cycle=evals / n,
+    fpp = eval_flops_per_point(prob.d, prob.K)
+    achieved, peak = evals * fpp / r["profile_seconds"] / 1e12, fpp / matrix_seconds_per_point(prob, cfg) / 1e12
+    out = dict(bound="mfma", achieved=achieved, peak=peak, unit="TFLOP/s",
+               frac=achieved / peak, evaluations_per_cycle=evals / n,
                ms_per_cycle=r["profile_seconds"] / n * 1e3,
                note="every objective evaluation a cycle performs (samples, line-search trials including the "
                     "speculative ones, smoothing probes) at K(2d^2+4d) flops each, over the whole cycle's time")
-    if peaks:
+    if peaks and not two_part_products(prob, cfg):
         out.update(peak_measured=peaks["fp32_mfma_tflops"], frac_measured=achieved / peaks["fp32_mfma_tflops"])
     return out
 
@@ -488,7 +523,7 @@ def main(argv=None):
 
     roof = eval_roofline(items, adj, peaks)
     roof_lbfgs = lbfgs_roofline(prob, cfg, adj, peaks)
-    cycle_roof = cycle_roofline(prob, adj, peaks)
+    cycle_roof = cycle_roofline(prob, cfg, adj, peaks)
     kernel_ms = {k: round(v["ms"] / args.profile_steps, 3) for k, v in adj["profile"].items() if v["launches"]}
 
     others = {}

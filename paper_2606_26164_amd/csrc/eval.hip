@@ -1,4 +1,4 @@
-// Batched mixture objective and adjoint gradient on FP32 MFMA (gfx950).
+// Batched mixture objective and adjoint gradient on MFMA (gfx950).
 //
 // For a point x and component k the kernel forms delta = x - mu_k (centring
 // before the product keeps FP32 cancellation out of the contraction) and
@@ -13,8 +13,10 @@
 // Work layout: a tile of 32 points in two 16-point blocks per wave (direct
 // evaluations may take 16-point half tiles; several waves share a line-search
 // tile or one of a small direct evaluation, each contracting a contiguous part
-// of the components, and their partial states are merged in wave order).  v_mfma_f32_16x16x4f32 computes U^T (DP x 16) = P' (DP x DP) *
-// Delta^T (DP x 16), P' the precision matrix with its rows permuted: lane l
+// of the components, and their partial states are merged in wave order).  In
+// float32 (the form in two f16 parts is described below) v_mfma_f32_16x16x4f32
+// computes U^T (DP x 16) = P' (DP x DP) * Delta^T (DP x 16), P' the precision
+// matrix with its rows permuted: lane l
 // supplies P[pi(16mb + l%16)][4ks + l/16] (A operand), pi(16mb + 4a + b) =
 // 4(4mb + b) + a, and delta[point l%16][4ks + l/16] (B operand), and receives
 // u at point l%16 and coordinate pi(16mb + 4(l/16) + r) = 4(4mb + r) + l/16,
@@ -139,9 +141,9 @@ struct CompRegs {
 // 1480 TFLOP/s) plus the vector instructions that split delta (two conversions
 // and two mixed multiply-adds a pair), which the matrix core does not hide.
 // 262144 points of the d = 64, K = 128 mixture, value and gradient: 2216 us in
-// float32, 856 us in two parts; a cycle of its 65536 samples 42.1 -> 19.1 ms.
+// float32, 856 us in two parts; a cycle of its 65536 samples 42.1 -> 19.1 ms
+// (before the shared components of large launches, see SHARE).
 //
-
 // f16 has 5 exponent bits, so operands are scaled by powers of two (exact):
 // coordinate j of points and centres by xs_j = 2^(e_j + b), the matrices by
 // 2^(kTwoPartP - e_i - e_j), with 4^e_j about max_k (P_k)_jj, so that scaled
@@ -1594,8 +1596,8 @@ __global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a)
 //
 // What bounds it: with waves enough the vector unit, about 100 instructions a
 // component of width 8 at 4 cycles each (two waves' instructions pair up only
-// where their registers allow it; 300000 points, K = 40: 50 us as tiles, 40
-// here); with few points one pass over the components, which the split
+// where their registers allow it; a call of 300000 points, K = 40: 45 us as
+// tiles, 36 here); with few points one pass over the components, which the split
 // shortens (16384 points, K = 40: 19.5 us as tiles, 16 unsplit, 7 split).  Two
 // points per lane were slower at every size (300000 points: 50 us).
 // ---------------------------------------------------------------------------
