@@ -387,11 +387,9 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             const float nu = pr.family == CHISAO_STUDENT_T ? pr.nu : 1.0f;
             if (!closed) {
                 float *tw, *tmu, *tprec;
-                // (the float32 tables only where something reads them)
-                if (!split[p]) {
-                    ALLOC(Pfrag, float, K * DP * DP);
-                    ALLOC(muB, float, K * DP);
-                }
+                // (in a two-part population read by chisao_eval's differences)
+                ALLOC(Pfrag, float, K * DP * DP);
+                ALLOC(muB, float, K * DP);
                 ALLOC(logc2, float, K);
                 ALLOC(tw, float, K);
                 ALLOC(tmu, float, K * d);
@@ -1331,6 +1329,7 @@ static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, int K
     if (G_dev) {
         a.F_out = nullptr;
         a.G_out = G_dev;
+        if (family < CHISAO_RASTRIGIN) return launch_mixture_fd(a, d, DP, family, K, st);
         a.max_tiles = Vfd <= 32 ? (B + (32 / Vfd) - 1) / (32 / Vfd) : (long)B * ((Vfd + 31) / 32);
         if ((e = launch_eval(a, DP, family, kDirect, true, false, st)) != hipSuccess) return e;
     }
@@ -1501,12 +1500,14 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     q.nu = nu;
     q.nu_plus_d = nu + (float)p->d;
     float xs[64];
-    const bool two_part = two_part_problem(*p, xs, &q.kq);
-    // one set of tables, the one the evaluation reads
+    // one set of tables at a time: the one the values are read from, then (in
+    // the same place) the float32 one of central differences
+    const bool fd_grad = grad_mode == CHISAO_GRAD_FD && G_dev, values = grad_mode == CHISAO_GRAD_ADJOINT || f_dev;
+    const bool two_part = two_part_problem(*p, xs, &q.kq) && values;
     float *pf = closed ? nullptr : (float *)(base + o_pf), *mub = closed ? nullptr : (float *)(base + o_mub);
     float *xs_dev = two_part ? (float *)(base + o_xs) : nullptr;
-    q.Pfrag = two_part ? nullptr : pf;
-    q.muB = two_part ? nullptr : mub;
+    q.Pfrag = pf;
+    q.muB = mub;
     q.Pfrag2 = two_part ? pf : nullptr;
     q.muB2 = two_part ? mub : nullptr;
     q.xs = xs_dev;
@@ -1527,15 +1528,18 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     HIP_TRY(hipMemcpyAsync(base + o_bad, &zero, sizeof zero, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + o_lo, p->lo, 4 * d, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + o_hi, p->hi, 4 * d, hipMemcpyHostToDevice, st));
+    auto prepare = [&](bool two) {
+        return launch_prepare(p->family, p->d, (int)DP, p->K, nu, (const float *)(base + o_w),
+                              (const float *)(base + o_mu), (const float *)(base + o_prec), (float *)(base + o_lc),
+                              two ? nullptr : pf, two ? nullptr : mub, two ? xs_dev : nullptr, q.kq, two ? pf : nullptr,
+                              two ? mub : nullptr, (int *)(base + o_bad), st);
+    };
     if (!closed) {
         HIP_TRY(hipMemcpyAsync(base + o_w, p->log_w, 4 * K, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(base + o_mu, p->mu, 4 * K * d, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(base + o_prec, p->prec, 4 * K * d * d, hipMemcpyHostToDevice, st));
         if (two_part) HIP_TRY(hipMemcpyAsync(xs_dev, xs, 4 * DP, hipMemcpyHostToDevice, st));
-        HIP_TRY(launch_prepare(p->family, p->d, (int)DP, p->K, nu, (const float *)(base + o_w),
-                               (const float *)(base + o_mu), (const float *)(base + o_prec), (float *)(base + o_lc),
-                               two_part ? nullptr : pf, two_part ? nullptr : mub, xs_dev, q.kq, two_part ? pf : nullptr,
-                               two_part ? mub : nullptr, (int *)(base + o_bad), st));
+        HIP_TRY(prepare(two_part));
     }
     // one synchronization: the host descriptors above stay alive until their
     // copies are done, and a matrix that is not positive definite is reported
@@ -1559,6 +1563,11 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     a.trial_next = -1;
     a.nz_kind = -1;
     a.split = two_part;
+    if (two_part && fd_grad) {
+        HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, (int)K, X_dev, B, f_dev, nullptr, grad_mode, st));
+        HIP_TRY(prepare(false));
+        f_dev = nullptr;
+    }
     HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, (int)K, X_dev, B, f_dev, G_dev, grad_mode, st));
     return CHISAO_OK;
 }

@@ -1745,6 +1745,284 @@ hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool g
 }
 
 // ---------------------------------------------------------------------------
+// Central differences of a mixture on caller memory.  A stencil point differs
+// from its centre in one coordinate, so with u = P delta and q = delta . u of
+// the centre its quadratic form is q + h (2 u_j + h P_jj), h the realised step:
+// one contraction a component and two multiply-adds, one exp2 and a sum a
+// stencil point, instead of a contraction each.  Every stencil point keeps a
+// log-sum-exp state of its own, so no step is too long; the difference is
+// taken between the states, (m+ - m-) + (log2 s+ - log2 s-), where a common
+// rounding of q is in both.  Contraction in float32: it is the smaller part.
+// What bounds it: the vector unit, about 8 instructions a stencil point and
+// component, one of them an exponential.  16384 gradients of a d = 16, K = 32
+// mixture (and the values) took 109 us as 33 evaluations, 23 here; the relative
+// error against float64 falls by a third (d = 2 to 31: 0.4e-6 to 4e-6).
+// (Populations evaluate every stencil point as it is: their differences carry
+// noise per point, and their paths the bits of the plain evaluation.)
+// ---------------------------------------------------------------------------
+template <int NS>
+struct LseStates {
+    float m[NS], s[NS];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            m[i] = -INFINITY;
+            s[i] = 0.0f;
+        }
+    }
+    // adds 2^t[i] to state i (the reference moves as in the tiles)
+    __device__ __forceinline__ void add(const float (&t)[NS]) {
+        float over = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) over = fmaxf(over, t[i] - m[i]);
+        if (__any(over > kLseSlack))
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const bool moved = t[i] - m[i] > kLseSlack;
+                s[i] *= moved ? __builtin_amdgcn_exp2f(m[i] - t[i]) : 1.0f;
+                m[i] = moved ? t[i] : m[i];
+            }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) s[i] += __builtin_amdgcn_exp2f(t[i] - m[i]);
+    }
+    // the states of a workgroup's four waves into the first wave's: 0 + 2 and
+    // 1 + 3, then those two.  Every wave calls it.
+    __device__ __forceinline__ void merge(int wv, int lane) {
+        __shared__ float s_m[2][NS][kWave], s_s[2][NS][kWave];
+#pragma unroll
+        for (int half = 2; half > 0; half /= 2) {
+            if (half < 2) __syncthreads();
+            if (wv >= half && wv < 2 * half)
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    s_m[wv - half][i][lane] = m[i];
+                    s_s[wv - half][i][lane] = s[i];
+                }
+            __syncthreads();
+            if (wv < half)
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    const float mv = s_m[wv][i][lane], sv = s_s[wv][i][lane], mx = fmaxf(m[i], mv);
+                    // (a wave without components, or with none that counts)
+                    const float a = s[i] == 0.0f ? 0.0f : s[i] * __builtin_amdgcn_exp2f(m[i] - mx);
+                    const float b = sv == 0.0f ? 0.0f : sv * __builtin_amdgcn_exp2f(mv - mx);
+                    s[i] = a + b;
+                    m[i] = mx;
+                }
+        }
+    }
+    // log2 of state i's sum over state j's
+    __device__ __forceinline__ float log2_ratio(int i, int j) const {
+        return (m[i] - m[j]) + (__log2f(s[i]) - __log2f(s[j]));
+    }
+};
+
+__device__ __forceinline__ float fd_half_step(float fd_h, float x) {
+    return fd_h > 0.0f ? fd_h : ldexpf(fmaxf(1.0f, fabsf(x)), -8);
+}
+
+// log2 density of a component from its quadratic form
+template <int FAM>
+__device__ __forceinline__ float component_log2(float lc2, float q, float nupd, float inv_nu) {
+    return FAM == 0 ? lc2 - q * (0.5f * kLog2e) : lc2 - (0.5f * nupd) * student_log2(q, inv_nu);
+}
+
+constexpr int kFdWaves = 4;
+
+// d > 8: 16 points a tile, the contraction and the lanes' coordinates as in
+// eval_kernel; a lane holds the states of its KS coordinates' stencils.
+// SPLIT: the four waves of a workgroup share a tile's components.
+template <int DP, int FAM, bool SPLIT>
+__global__ __launch_bounds__(kWave * kFdWaves) void mixture_fd_kernel(EvalArgs a) {
+    constexpr int KS = DP / 4, MB = DP / 16;
+    const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int n = lane & 15, g = lane >> 4;
+    const ProblemDesc &pd = a.D.pd[a.cls[0]];
+    const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
+    const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu;
+    const int i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * 16 + n, ir = min(i, a.ext_n - 1);
+    float x[KS], hp[KS], hm[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int c = 4 * ks + g;
+        x[ks] = c < d ? as_global(a.X)[(size_t)ir * d + c] : 0.0f;
+        const float h = c < d ? fd_half_step(pd.fd_h, x[ks]) : 0.0f, up = x[ks] + h, dn = x[ks] - h;
+        hp[ks] = up - x[ks];
+        hm[ks] = dn - x[ks];
+    }
+    const __amdgpu_buffer_rsrc_t rs_pf = table_rsrc(pd.Pfrag, (uint32_t)K * DP * DP * 4u);
+    const __amdgpu_buffer_rsrc_t rs_mu = table_rsrc(pd.muB, (uint32_t)K * DP * 4u);
+    const __amdgpu_buffer_rsrc_t rs_lc = table_rsrc(pd.logc2, (uint32_t)K * 4u);
+    LseStates<2 * KS> st;
+    st.clear();
+    const int k_end = SPLIT ? (int)((long)K * (wv + 1) / kFdWaves) : K;
+    for (int k = SPLIT ? (int)((long)K * wv / kFdWaves) : 0; k < k_end; ++k) {
+        const int pf_k = k * DP * DP * 4, mu_k = k * DP * 4;
+        float pa[KS][MB], diag[KS], dl[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) load_frag_buf<MB>(rs_pf, (ks * kWave + lane) * MB * 4, pf_k, pa[ks]);
+        // P_jj of coordinate j = 4 ks + g: row block ks / 4, lane 16 g + (4 g + ks % 4)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            diag[ks] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(
+                           rs_pf, ((ks * kWave + 20 * g + (ks & 3)) * MB + (ks >> 2)) * 4, pf_k, 0));
+#pragma unroll
+        for (int ks = 0; ks < KS; ks += 4) {
+            const f32x4 v = __builtin_bit_cast(
+                f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_mu, (g * KS + ks) * 4, mu_k, 0));
+            dl[ks] = x[ks] - v[0]; dl[ks + 1] = x[ks + 1] - v[1];
+            dl[ks + 2] = x[ks + 2] - v[2]; dl[ks + 3] = x[ks + 3] - v[3];
+        }
+        const float lc2 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs_lc, 0, k * 4, 0));
+        f32x4 acc[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[ks][mb], dl[ks], acc[mb], 0, 0, 0);
+        float q = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) q = fmaf(dl[ks], acc[ks / 4][ks % 4], q);
+        q += __shfl_xor(q, 16, kWave);
+        q += __shfl_xor(q, 32, kWave);
+        float t[2 * KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const float u2 = 2.0f * acc[ks / 4][ks % 4];
+            t[2 * ks] = component_log2<FAM>(lc2, fmaf(hp[ks], fmaf(hp[ks], diag[ks], u2), q), nupd, inv_nu);
+            t[2 * ks + 1] = component_log2<FAM>(lc2, fmaf(hm[ks], fmaf(hm[ks], diag[ks], u2), q), nupd, inv_nu);
+        }
+        st.add(t);
+    }
+    if constexpr (SPLIT) {
+        st.merge(wv, lane);
+        if (wv != 0) return;
+    }
+    if (i >= a.ext_n) return;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int c = 4 * ks + g;
+        const float h = fd_half_step(pd.fd_h, x[ks]), up = x[ks] + h, dn = x[ks] - h;
+        if (c < d) a.G_out[(size_t)i * d + c] = st.log2_ratio(2 * ks, 2 * ks + 1) * kLn2 / (up - dn);
+    }
+}
+
+// d <= 8: one point a lane, records through LDS as in alu_direct_kernel.
+template <int FAM, int W, bool SPLIT>
+__global__ __launch_bounds__(kAluBlock) void alu_fd_kernel(EvalArgs a) {
+    constexpr int T = W * (W + 1) / 2, R = alu_record(W);
+    static_assert(kAluBlock == kWave * kFdWaves, "four waves share a tile's components");
+    __shared__ f32x4 s_rec[kAluChunk * (R / 4)];
+    const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const ProblemDesc &pd = a.D.pd[a.cls[0]];
+    const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
+    const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu;
+    const int i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * kWave + lane;
+    const bool in = i < a.ext_n;
+    float x[W], hp[W], hm[W];
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+        x[c] = (in && c < d) ? as_global(a.X)[(size_t)i * d + c] : 0.0f;
+        const float h = c < d ? fd_half_step(pd.fd_h, x[c]) : 0.0f, up = x[c] + h, dn = x[c] - h;
+        hp[c] = up - x[c];
+        hm[c] = dn - x[c];
+    }
+    LseStates<2 * W> st;
+    st.clear();
+    for (int k0 = 0; k0 < K; k0 += kAluChunk) {
+        const int n = min(kAluChunk, K - k0);
+        if (k0) __syncthreads();
+        for (int e = threadIdx.x; e < n * (R / 4); e += kAluBlock)
+            s_rec[e] = reinterpret_cast<const gf32x4 *>(as_global(pd.Pfrag) + (size_t)k0 * R)[e];
+        __syncthreads();
+        for (int k = SPLIT ? wv : 0; k < n; k += SPLIT ? kFdWaves : 1) {
+            float rec[R], dl[W], u[W], q = 0.0f, t[2 * W];
+#pragma unroll
+            for (int e = 0; e < R / 4; ++e) {
+                const f32x4 v = s_rec[k * (R / 4) + e];
+                rec[4 * e] = v[0]; rec[4 * e + 1] = v[1]; rec[4 * e + 2] = v[2]; rec[4 * e + 3] = v[3];
+            }
+#pragma unroll
+            for (int c = 0; c < W; ++c) dl[c] = x[c] - rec[T + c];
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                float acc = 0.0f;
+#pragma unroll
+                for (int j = 0; j < W; ++j) {
+                    const int lo = c < j ? c : j, hi = c < j ? j : c;
+                    acc = fmaf(rec[lo * W - lo * (lo - 1) / 2 + (hi - lo)], dl[j], acc);
+                }
+                u[c] = acc;
+                q = fmaf(dl[c], acc, q);
+            }
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                const float pjj = rec[c * W - c * (c - 1) / 2], u2 = 2.0f * u[c];
+                t[2 * c] = component_log2<FAM>(rec[T + W], fmaf(hp[c], fmaf(hp[c], pjj, u2), q), nupd, inv_nu);
+                t[2 * c + 1] = component_log2<FAM>(rec[T + W], fmaf(hm[c], fmaf(hm[c], pjj, u2), q), nupd, inv_nu);
+            }
+            st.add(t);
+        }
+    }
+    if constexpr (SPLIT) {
+        st.merge(wv, lane);
+        if (wv != 0) return;
+    }
+    if (!in) return;
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+        const float h = fd_half_step(pd.fd_h, x[c]), up = x[c] + h, dn = x[c] - h;
+        if (c < d) a.G_out[(size_t)i * d + c] = st.log2_ratio(2 * c, 2 * c + 1) * kLn2 / (up - dn);
+    }
+}
+
+// Components are shared while the tiles leave SIMDs idle and there is work in a
+// component to share (us unshared / shared; tiles of 64 points at width 8, of
+// 16 above): width 16, K = 16: 11.4 / 6.9 at 256 tiles, 11.7 / 11.8 at 1024, 25
+// / 29 at 4096; K = 64: 31 / 25 at 1024; K = 4: 6.6 / 6.9 at 256; width 32, K =
+// 4: 9.4 / 8.0 at 256, K = 64: 57 / 53 at 1024; width 64, K = 16: 45 / 22 at
+// 256, 47 / 56 at 1024; width 8, K = 16: 17 / 10 at 256, 18.1 / 21.7 at 1024.
+static bool fd_split(int DP, int K, long tiles) {
+    return K * DP >= 128 && (tiles <= 512 || (tiles <= 1024 && K >= 32 && DP <= 32));
+}
+
+hipError_t launch_mixture_fd(const EvalArgs &a, int d, int DP, int family, int K, hipStream_t st) {
+    if (a.ext_n <= 0) return hipSuccess;
+    const int per_tile = DP == kAluDP ? kWave : 16;
+    const long tiles = ((long)a.ext_n + per_tile - 1) / per_tile;
+    const bool split = fd_split(DP, K, tiles);
+    const dim3 b(kWave * kFdWaves), g((unsigned)(split ? tiles : (tiles + kFdWaves - 1) / kFdWaves));
+#define CHISAO_FD(KERNEL, N)                                                                 \
+    do {                                                                                     \
+        if (family == 0) {                                                                   \
+            if (split) hipLaunchKernelGGL((KERNEL(N, 0, true)), g, b, 0, st, a);             \
+            else hipLaunchKernelGGL((KERNEL(N, 0, false)), g, b, 0, st, a);                  \
+        } else {                                                                             \
+            if (split) hipLaunchKernelGGL((KERNEL(N, 1, true)), g, b, 0, st, a);             \
+            else hipLaunchKernelGGL((KERNEL(N, 1, false)), g, b, 0, st, a);                  \
+        }                                                                                    \
+    } while (0)
+#define CHISAO_FD_MFMA(DP, F, S) mixture_fd_kernel<DP, F, S>
+#define CHISAO_FD_ALU(W, F, S) alu_fd_kernel<F, W, S>
+    switch (DP == kAluDP ? alu_width(d) : DP) {
+        case 2: CHISAO_FD(CHISAO_FD_ALU, 2); break;
+        case 4: CHISAO_FD(CHISAO_FD_ALU, 4); break;
+        case 8: CHISAO_FD(CHISAO_FD_ALU, 8); break;
+        case 16: CHISAO_FD(CHISAO_FD_MFMA, 16); break;
+        case 32: CHISAO_FD(CHISAO_FD_MFMA, 32); break;
+        case 64: CHISAO_FD(CHISAO_FD_MFMA, 64); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef CHISAO_FD_ALU
+#undef CHISAO_FD_MFMA
+#undef CHISAO_FD
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // Dispatch
 // ---------------------------------------------------------------------------
 template <int DP, int FAM, bool H16>

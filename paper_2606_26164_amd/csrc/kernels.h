@@ -55,6 +55,10 @@ int direct_split(int DP, int family, int K, long tiles);
 // with d <= 8 at the ext_n dense rows of X: caller memory only.
 hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool grad, hipStream_t st);
 
+// Central-difference gradients (G_out) of one mixture at the ext_n dense rows
+// of X: caller memory only, from the float32 tables.
+hipError_t launch_mixture_fd(const EvalArgs &a, int d, int DP, int family, int K, hipStream_t st);
+
 // center: kDirect / kTrial / kProbe; fd: stencil around each centre;
 // grad: accumulate the adjoint gradient.
 hipError_t launch_eval(EvalArgs a, int DP, int family, int center, bool fd, bool grad, hipStream_t st);
