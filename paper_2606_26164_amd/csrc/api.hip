@@ -845,16 +845,25 @@ static hipError_t eval_list_class(chisao_ctx *h, const EvalClass &c, hipStream_t
     return run_eval(h, c, a, kDirect, true, false, st);
 }
 
+// Classes of moderate size take all trials after the first in one launch: the
+// launch saved (with its compaction) is worth more than trials that a search
+// accepting t = 1/2 or 1/4 does not use.  ms a cycle, staged / merged: width 8
+// (K = 40) 2.14 / 1.77 with 32768 samples; width 16 (K = 32) 1.34 / 1.17 with
+// 16384, 2.45 / 2.34 with 65536; width 32 (K = 32) 1.57 / 1.47 with 16384, 2.15
+// / 2.22 with 32768; width 64 (K = 32) 1.84 / 1.78 with 8192, 2.37 / 2.46 with
+// 16384.  Evaluation counts stay those of the stages (trial_need).
+static int trial_merge_max(int DP) { return DP <= 16 ? 65536 : (DP == 32 ? 16384 : 8192); }
+
 // Small classes keep the active list through Phase 1 and pick the jobs of each
 // launch out of it by their flags.  Their launches are as long as their
 // latency, so a tile that is partly (or all) idle costs nothing, and the list
-// compactions, four of the eight launches of an iteration, would.  Per cycle: a
-// d = 6 problem of 256 samples 314 -> 283 us; K = 40, d = 8: 1.69 -> 1.47 ms
-// with 4096 samples, 1.91 -> 1.69 with 16384; K = 32, d = 16: 1.16 -> 1.09 with
-// 4096, but 1.43 -> 1.79 with 16384; wider ones gain nothing at 4096 and lose
-// from 8192 on (K = 48, d = 32: 1.50 -> 1.66): there the idle tiles of the later
-// search stages cost more than the compactions.
-static int in_place_max(int DP) { return DP == kAluDP ? 16384 : (DP == 16 ? 4096 : 2048); }
+// compactions, three of the six launches of an iteration, would.  ms a cycle,
+// lists / in place: d = 6, K = 6 0.72 / 0.60 with 256 samples; width 8 (K = 40)
+// 1.43 / 1.39 with 16384, 1.77 / 1.97 with 32768; width 16 0.88 / 0.81 with
+// 2048, 0.92 / 0.94 with 4096; width 32 1.06 / 1.02 with 1024, 1.08 / 1.25 with
+// 4096; width 64 gains nothing at 256 (K = 32: 1.72 / 1.77; K = 128: 4.25 /
+// 4.51): there the idle tiles cost more than the compactions.
+static int in_place_max(int DP) { return DP == kAluDP ? 16384 : (DP == 16 ? 2048 : (DP == 32 ? 1024 : 0)); }
 
 // Iteration t of Phase 1 for one evaluation class, on the stream st (t runs
 // to the class's own n_conv + 1, which closes the last iteration).
@@ -887,15 +896,18 @@ static hipError_t converge_iteration(chisao_ctx *h, const EvalClass &c, hipStrea
     // those too.  Most searches that reject t = 1 accept one of the next two,
     // so evaluating every remaining trial at once would mostly compute points
     // that are never used.
-    for (int stage = 0; stage < 3; ++stage) {
+    // (up to trial_merge_max samples that is still the shorter way)
+    const bool two = c.n <= trial_merge_max(c.DP);
+    for (int stage = 0; stage < (two ? 2 : 3); ++stage) {
         const int lst = in_place ? L_ACT : (stage == 0 ? list_out : (stage == 1 ? L_T2 : L_T3));
         EvalArgs a = base_args(h, c);
         a.list_id = lst;
         a.by_flag = in_place ? 1 : 0;
         a.vc_kind = stage == 0 ? kVcTrialFirst : kVcTrialRest;
         a.trial_lo = stage == 0 ? 0 : (stage == 1 ? 1 : 3);
-        a.trial_cnt = stage == 0 ? 0 : (stage == 1 ? 2 : kMaxTrials);
-        a.trial_next = stage == 0 ? L_T2 : (stage == 1 ? L_T3 : -1);
+        a.trial_cnt = stage == 0 ? 0 : (stage == 1 && !two ? 2 : kMaxTrials);
+        a.trial_next = stage == 0 ? L_T2 : (stage == 1 && !two ? L_T3 : -1);
+        a.trial_need = stage == 1 && two ? 2 : 0;
         a.step = t;
         a.nz_kind = 0;
         if ((e = run_eval(h, c, a, kTrial, false, adj, st)) != hipSuccess) return e;

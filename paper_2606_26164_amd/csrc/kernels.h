@@ -32,6 +32,8 @@ struct EvalArgs {
     float *G_out;         // direct centres: gradient rows (may be null)
     int out_stride;
     int trial_next;       // trial centres: -1 when no later stage follows (a search none of whose trials passes fails)
+    int trial_need;           // > 0: a search that accepts one of the launch's first trial_need trials counts those
+                              // as evaluated, as if the others were launched after them
     int trial_lo, trial_cnt;  // kVcTrialRest: trials trial_lo .. trial_lo + trial_cnt - 1, capped at ls_max
     int need_bit;         // phase_mask bit a problem must have set to take part (0: none)
     int step_limit;       // 1: only problems with step < n_cloud, 2: step < n_anti, 0: all
