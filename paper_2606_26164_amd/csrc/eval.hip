@@ -1623,8 +1623,8 @@ __global__ __launch_bounds__(kAluBlock) void alu_direct_kernel(EvalArgs a) {
     const ProblemDesc &pd = a.D.pd[a.cls[0]];
     const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
     const float nu = pd.nu, nupd = pd.nu_plus_d, inv_nu = 1.0f / nu;
-    const int i = (SPLIT > 1 ? blockIdx.x : blockIdx.x * kWaves + wv) * kWave + lane;
-    const bool in = i < a.ext_n;
+    const uint32_t i = (SPLIT > 1 ? blockIdx.x : blockIdx.x * kWaves + wv) * kWave + lane;
+    const bool in = i < (uint32_t)a.ext_n;
     float xr[W], ga[GRAD ? W : 1], m = -INFINITY, sm = 0.0f;
 #pragma unroll
     for (int c = 0; c < W; ++c) {
@@ -1852,7 +1852,7 @@ __global__ __launch_bounds__(kWave * kFdWaves) void mixture_fd_kernel(EvalArgs a
     const ProblemDesc &pd = a.D.pd[a.cls[0]];
     const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
     const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu;
-    const int i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * 16 + n, ir = min(i, a.ext_n - 1);
+    const uint32_t i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * 16 + n, ir = min(i, (uint32_t)a.ext_n - 1);
     float x[KS], hp[KS], hm[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -1913,7 +1913,7 @@ __global__ __launch_bounds__(kWave * kFdWaves) void mixture_fd_kernel(EvalArgs a
         st.merge(wv, lane);
         if (wv != 0) return;
     }
-    if (i >= a.ext_n) return;
+    if (i >= (uint32_t)a.ext_n) return;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const int c = 4 * ks + g;
@@ -1932,8 +1932,8 @@ __global__ __launch_bounds__(kAluBlock) void alu_fd_kernel(EvalArgs a) {
     const ProblemDesc &pd = a.D.pd[a.cls[0]];
     const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
     const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu;
-    const int i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * kWave + lane;
-    const bool in = i < a.ext_n;
+    const uint32_t i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * kWave + lane;
+    const bool in = i < (uint32_t)a.ext_n;
     float x[W], hp[W], hm[W];
 #pragma unroll
     for (int c = 0; c < W; ++c) {
