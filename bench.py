@@ -589,6 +589,8 @@ def main(argv=None):
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
+        "contraction": "float32 operands as two f16 parts each, float32 sums" if two_part_products(prob, cfg)
+                       else "float32 products",
         "data": "synthetic",
         "config": {
             "workload": f"d=64 anisotropic Gaussian mixture, K=128, N={cfg.N}; m=10, n_conv=18, "
