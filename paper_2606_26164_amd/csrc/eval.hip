@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "ranges.h"
 
 namespace chisao {
 
@@ -386,11 +387,12 @@ __device__ __forceinline__ int centres(const EvalArgs &a, const ProblemDesc &pd)
     }
 }
 // inclusive prefix sum over the wave
-__device__ __forceinline__ int wave_scan(int v) {
+template <class T>
+__device__ __forceinline__ T wave_scan(T v) {
     const int l = threadIdx.x % kWave;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-        const int u = __shfl_up(v, o, kWave);
+        const T u = __shfl_up(v, o, kWave);
         if (l >= o) v += u;
     }
     return v;
@@ -1481,36 +1483,36 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
 constexpr int kCfdWaves = 4;  // waves (centres at a time) per workgroup
 template <int CENTER>
 __global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a) {
-    __shared__ int s_pref[kMaxClass + 1];
+    __shared__ unit_t s_pref[kMaxClass + 1];
     __shared__ f32x4 s_row[kCfdWaves][kWave];  // per coordinate: centre, its two factors
     const Dev &D = a.D;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     const bool ext = a.ext_n >= 0;
     if (wv == 0) {
-        int carry = 0;
+        unit_t carry = 0;
         if (lane == 0) s_pref[0] = 0;
         for (int j0 = 0; j0 < a.n_cls; j0 += kWave) {
             const int j = j0 + lane;
-            int t = 0;
+            unit_t t = 0;
             if (j < a.n_cls) {
                 const int p = a.cls[j];
                 const ProblemDesc &pd = D.pd[p];
-                t = job_count(a, p, pd) * centres(a, pd);
+                t = units_of(job_count(a, p, pd), centres(a, pd));
                 if (blockIdx.x == 0 && !ext && t > 0 && !a.by_flag) {
                     const unsigned long long nv = (unsigned long long)t * (unsigned long long)(2 * pd.d);
                     atomicAdd(&D.ctl[p].evals, nv);
                     atomicAdd(&D.prof[CHISAO_PROF_EVAL_FD], nv);
                 }
             }
-            const int inc = wave_scan(t);
+            const unit_t inc = wave_scan(t);
             if (j < a.n_cls) s_pref[j + 1] = carry + inc;
             carry += __shfl(inc, kWave - 1, kWave);
         }
     }
     __syncthreads();
-    const int total = s_pref[a.n_cls];
+    const unit_t total = s_pref[a.n_cls];
     // (no barrier inside the loop: a wave's rows of s_row are its own)
-    for (int u = blockIdx.x * kCfdWaves + wv; u < total; u += gridDim.x * kCfdWaves) {
+    for (unit_t u = first_unit(blockIdx.x, kCfdWaves, wv); u < total; u = next_unit(u, gridDim.x, kCfdWaves)) {
         int lo_j = 0, hi_j = a.n_cls - 1;
         while (lo_j < hi_j) {
             const int mid = (lo_j + hi_j + 1) >> 1;
@@ -1519,8 +1521,11 @@ __global__ __launch_bounds__(kWave *kCfdWaves) void closed_fd_kernel(EvalArgs a)
         }
         const int p = __builtin_amdgcn_readfirstlane(a.cls[lo_j]);
         const ProblemDesc &pd = D.pd[p];
-        const int d = pd.d, fam = pd.family, Vc = centres(a, pd);
-        const int job = (u - s_pref[lo_j]) / Vc, ci = (u - s_pref[lo_j]) % Vc;
+        const int d = pd.d, fam = pd.family;
+        // (one centre a job unless the jobs' centres are probes)
+        const unit_t v = u - s_pref[lo_j];
+        const int Vc = CENTER == kProbe ? centres(a, pd) : 1;
+        const int job = (int)(v / Vc), ci = (int)(v % Vc);
         const int s = ext ? job : (a.list_id >= 0 ? list_ptr(D, a.list_id, pd.s0)[job] : pd.s0 + job);
         const uint32_t kcyc = (uint32_t)D.ctl[p].k + 1u;
         if (a.by_flag) {
