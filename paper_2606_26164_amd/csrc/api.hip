@@ -1319,7 +1319,7 @@ static hipError_t ext_eval_launches(EvalArgs a, int d, int DP, int family, int K
     a.ext_n = B;
     a.vc_kind = kVcOne;
     const long Vfd = 2 * d;
-    const long tiles = (B + 31) / 32;
+    const long tiles = ((long)B + 31) / 32;
     hipError_t e;
     if (grad_mode == CHISAO_GRAD_ADJOINT) {
         a.F_out = f_dev;

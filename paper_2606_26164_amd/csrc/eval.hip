@@ -1735,7 +1735,7 @@ __global__ __launch_bounds__(kAluBlock) void alu_direct_kernel(EvalArgs a) {
 // points (K = 16: 8.7 against 9.8 us there, 13.3 against 12.6 at 131072).
 template <int FAM, bool GRAD, int W>
 static hipError_t alu_direct_width(const EvalArgs &a, int K, hipStream_t st) {
-    const long groups = (a.ext_n + kWave - 1) / kWave;
+    const long groups = ((long)a.ext_n + kWave - 1) / kWave;
     constexpr int kWaves = kAluBlock / kWave;
     const dim3 b(kAluBlock), each((unsigned)((groups + kWaves - 1) / kWaves)), shared((unsigned)groups);
     if (K >= 32 || (K >= 8 && groups <= 1024))
@@ -1745,8 +1745,22 @@ static hipError_t alu_direct_width(const EvalArgs &a, int K, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool grad, hipStream_t st) {
-    if (a.ext_n <= 0) return hipSuccess;
+// fn for each launch's rows of a call on caller memory
+template <class F>
+static hipError_t for_launch_rows(EvalArgs a, int d, F &&fn) {
+    for (int left = a.ext_n; left > 0;) {
+        a.ext_n = launch_rows(left);
+        const hipError_t e = fn(a);
+        if (e != hipSuccess) return e;
+        left -= a.ext_n;
+        a.X += (size_t)a.ext_n * d;
+        if (a.F_out) a.F_out += a.ext_n;
+        if (a.G_out) a.G_out += (size_t)a.ext_n * d;
+    }
+    return hipSuccess;
+}
+
+static hipError_t alu_direct_rows(const EvalArgs &a, int d, int family, int K, bool grad, hipStream_t st) {
 #define CHISAO_ALU(F, G)                                                  \
     switch (alu_width(d)) {                                               \
         case 2: return alu_direct_width<F, G, 2>(a, K, st);               \
@@ -1759,6 +1773,10 @@ hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool g
         if (grad) CHISAO_ALU(1, true) else CHISAO_ALU(1, false)
     }
 #undef CHISAO_ALU
+}
+
+hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool grad, hipStream_t st) {
+    return for_launch_rows(a, d, [&](const EvalArgs &r) { return alu_direct_rows(r, d, family, K, grad, st); });
 }
 
 // ---------------------------------------------------------------------------
@@ -2006,8 +2024,7 @@ static bool fd_split(int DP, int K, long tiles) {
     return K * DP >= 128 && (tiles <= 512 || (tiles <= 1024 && K >= 32 && DP <= 32));
 }
 
-hipError_t launch_mixture_fd(const EvalArgs &a, int d, int DP, int family, int K, hipStream_t st) {
-    if (a.ext_n <= 0) return hipSuccess;
+static hipError_t mixture_fd_rows(const EvalArgs &a, int d, int DP, int family, int K, hipStream_t st) {
     const int per_tile = DP == kAluDP ? kWave : 16;
     const long tiles = ((long)a.ext_n + per_tile - 1) / per_tile;
     const bool split = fd_split(DP, K, tiles);
@@ -2037,6 +2054,10 @@ hipError_t launch_mixture_fd(const EvalArgs &a, int d, int DP, int family, int K
 #undef CHISAO_FD_MFMA
 #undef CHISAO_FD
     return hipGetLastError();
+}
+
+hipError_t launch_mixture_fd(const EvalArgs &a, int d, int DP, int family, int K, hipStream_t st) {
+    return for_launch_rows(a, d, [&](const EvalArgs &r) { return mixture_fd_rows(r, d, DP, family, K, st); });
 }
 
 // ---------------------------------------------------------------------------

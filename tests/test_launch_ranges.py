@@ -44,3 +44,18 @@ def test_every_wave_ends_at_the_last_unit(tmp_path, jobs, centres):
         CHECK(next_unit(u, blocks, waves) >= total);
     }}
     CHECK(last == total - 1);""")
+
+
+@pytest.mark.parametrize("rows", [1, 2**29 - 1, 2**29, 2**29 + 1, 2**30, 2**30 + 1, 2**31 - 64, 2**31 - 1])
+def test_launches_cover_the_rows_within_hips_limit(tmp_path, rows):
+    """Every row once, in parts of one size whose four threads a row stay below
+    HIP's 2^32 threads a launch."""
+    _run(tmp_path, f"""
+    long long at = 0; int left = {rows}, first = launch_rows(left), n = 0;
+    while (left > 0) {{
+        const int r = launch_rows(left);
+        CHECK(r > 0 && r <= left && first - r >= 0 && first - r <= 4);
+        CHECK((unsigned long long)r * kThreadsPerRow + 1023 < 1ull << 32);
+        at += r; left -= r; ++n;
+    }}
+    CHECK(at == {rows}ll && n == ({rows}ll + kLaunchRows - 1) / kLaunchRows);""")
