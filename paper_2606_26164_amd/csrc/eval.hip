@@ -1785,12 +1785,21 @@ hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool g
 // the centre its quadratic form is q + h (2 u_j + h P_jj), h the realised step:
 // one contraction a component and two multiply-adds, one exp2 and a sum a
 // stencil point, instead of a contraction each.  Every stencil point keeps a
-// log-sum-exp state of its own, so no step is too long; the difference is
-// taken between the states, (m+ - m-) + (log2 s+ - log2 s-), where a common
-// rounding of q is in both.  Contraction in float32: it is the smaller part.
+// log-sum-exp state of its own; the difference is taken between the states,
+// (m+ - m-) + (log2 s+ - log2 s-), where a common rounding of q is in both.
+// Contraction in float32: it is the smaller part.
+//
+// A step that leads from far away to next to a component's centre leaves a
+// difference of large numbers in that formula, off by a rounding of the
+// centre's q.  A stencil point whose form is less than half of a centre's that
+// is more than kFdTrust (long_step) is therefore contracted itself, from its
+// own delta.  That takes a step of more than (1 - 1/sqrt 2) sqrt(q), at least
+// 1.2 standard deviations of the component, so ordinary steps never do it, and
+// a wave in which every one does costs what evaluating its points costs.
+//
 // What bounds it: the vector unit, about 8 instructions a stencil point and
 // component, one of them an exponential.  16384 gradients of a d = 16, K = 32
-// mixture (and the values) took 109 us as 33 evaluations, 23 here; the relative
+// mixture (and the values) took 109 us as 33 evaluations, 24 here; the relative
 // error against float64 falls by a third (d = 2 to 31: 0.4e-6 to 4e-6).
 // (Populations evaluate every stencil point as it is: their differences carry
 // noise per point, and their paths the bits of the plain evaluation.)
@@ -1862,6 +1871,20 @@ __device__ __forceinline__ float component_log2(float lc2, float q, float nupd, 
     return FAM == 0 ? lc2 - q * (0.5f * kLog2e) : lc2 - (0.5f * nupd) * student_log2(q, inv_nu);
 }
 
+// Centres whose form is below it are off by roundings of 16 at most, as a value
+// is by its other terms; a Student-t density is log1p(q / nu), so there the
+// form counts in units of nu too.
+constexpr float kFdTrust = 16.0f;
+template <int FAM>
+__device__ __forceinline__ float fd_trust(float nu) {
+    return FAM == 0 ? kFdTrust : fminf(kFdTrust, 4.0f * nu);
+}
+// whether a stencil point's form t is not to be had from its centre's q (an
+// overflown q says nothing of t; a NaN stays one either way)
+__device__ __forceinline__ bool long_step(float t, float q, float trust) {
+    return q > trust && !(t >= 0.5f * q && q < INFINITY);
+}
+
 constexpr int kFdWaves = 4;
 
 // d > 8: 16 points a tile, the contraction and the lanes' coordinates as in
@@ -1874,7 +1897,7 @@ __global__ __launch_bounds__(kWave * kFdWaves) void mixture_fd_kernel(EvalArgs a
     const int n = lane & 15, g = lane >> 4;
     const ProblemDesc &pd = a.D.pd[a.cls[0]];
     const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
-    const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu;
+    const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu, trust = fd_trust<FAM>(pd.nu);
     const uint32_t i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * 16 + n, ir = min(i, (uint32_t)a.ext_n - 1);
     float x[KS], hp[KS], hm[KS];
 #pragma unroll
@@ -1923,13 +1946,57 @@ __global__ __launch_bounds__(kWave * kFdWaves) void mixture_fd_kernel(EvalArgs a
         for (int ks = 0; ks < KS; ++ks) q = fmaf(dl[ks], acc[ks / 4][ks % 4], q);
         q += __shfl_xor(q, 16, kWave);
         q += __shfl_xor(q, 32, kWave);
-        float t[2 * KS];
+        float t[2 * KS], low = q;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const float u2 = 2.0f * acc[ks / 4][ks % 4];
-            t[2 * ks] = component_log2<FAM>(lc2, fmaf(hp[ks], fmaf(hp[ks], diag[ks], u2), q), nupd, inv_nu);
-            t[2 * ks + 1] = component_log2<FAM>(lc2, fmaf(hm[ks], fmaf(hm[ks], diag[ks], u2), q), nupd, inv_nu);
+            t[2 * ks] = fmaf(hp[ks], fmaf(hp[ks], diag[ks], u2), q);
+            t[2 * ks + 1] = fmaf(hm[ks], fmaf(hm[ks], diag[ks], u2), q);
+            low = fminf(low, fminf(t[2 * ks], t[2 * ks + 1]));
         }
+        if (__any(long_step(low, q, trust)))
+#pragma clang loop unroll(disable)
+            for (int i = 0; i < 2 * KS; ++i) {
+                const int ks = i >> 1;
+                float own = 0.0f, ti = 0.0f;
+#pragma unroll
+                for (int j = 0; j < KS; ++j) {
+                    own = j == ks ? x[j] : own;
+                    ti = j == ks ? ((i & 1) ? t[2 * j + 1] : t[2 * j]) : ti;
+                }
+                const bool mine = 4 * ks + g < d && long_step(ti, q, trust);
+                if (!__any(mine)) continue;
+                const float h = fd_half_step(pd.fd_h, own);
+                own = ((i & 1) ? own - h : own + h) -
+                      __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs_mu, (g * KS + ks) * 4, mu_k, 0));
+                // the four lanes of a point hold four coordinates: one contraction each
+#pragma clang loop unroll(disable)
+                for (int gg = 0; gg < 4; ++gg) {
+                    if (!__any(mine && g == gg)) continue;
+                    f32x4 acc1[MB];
+                    float dl1[KS], q1 = 0.0f;
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) acc1[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < KS; ++j) {
+                        dl1[j] = (j == ks && g == gg) ? own : dl[j];
+                        float pj[MB];
+                        load_frag_buf<MB>(rs_pf, (j * kWave + lane) * MB * 4, pf_k, pj);
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb)
+                            acc1[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(pj[mb], dl1[j], acc1[mb], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int j = 0; j < KS; ++j) q1 = fmaf(dl1[j], acc1[j / 4][j % 4], q1);
+                    q1 += __shfl_xor(q1, 16, kWave);
+                    q1 += __shfl_xor(q1, 32, kWave);
+                    ti = mine && g == gg ? q1 : ti;
+                }
+#pragma unroll
+                for (int j = 0; j < 2 * KS; ++j) t[j] = j == i ? ti : t[j];
+            }
+#pragma unroll
+        for (int i = 0; i < 2 * KS; ++i) t[i] = component_log2<FAM>(lc2, t[i], nupd, inv_nu);
         st.add(t);
     }
     if constexpr (SPLIT) {
@@ -1954,7 +2021,7 @@ __global__ __launch_bounds__(kAluBlock) void alu_fd_kernel(EvalArgs a) {
     const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const ProblemDesc &pd = a.D.pd[a.cls[0]];
     const int d = pd.d, K = __builtin_amdgcn_readfirstlane(pd.K);
-    const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu;
+    const float nupd = pd.nu_plus_d, inv_nu = 1.0f / pd.nu, trust = fd_trust<FAM>(pd.nu);
     const uint32_t i = (SPLIT ? blockIdx.x : blockIdx.x * kFdWaves + wv) * kWave + lane;
     const bool in = i < (uint32_t)a.ext_n;
     float x[W], hp[W], hm[W];
@@ -1993,12 +2060,45 @@ __global__ __launch_bounds__(kAluBlock) void alu_fd_kernel(EvalArgs a) {
                 u[c] = acc;
                 q = fmaf(dl[c], acc, q);
             }
+            float low = q;
 #pragma unroll
             for (int c = 0; c < W; ++c) {
                 const float pjj = rec[c * W - c * (c - 1) / 2], u2 = 2.0f * u[c];
-                t[2 * c] = component_log2<FAM>(rec[T + W], fmaf(hp[c], fmaf(hp[c], pjj, u2), q), nupd, inv_nu);
-                t[2 * c + 1] = component_log2<FAM>(rec[T + W], fmaf(hm[c], fmaf(hm[c], pjj, u2), q), nupd, inv_nu);
+                t[2 * c] = fmaf(hp[c], fmaf(hp[c], pjj, u2), q);
+                t[2 * c + 1] = fmaf(hm[c], fmaf(hm[c], pjj, u2), q);
+                low = fminf(low, fminf(t[2 * c], t[2 * c + 1]));
             }
+            if (__any(long_step(low, q, trust)))
+#pragma clang loop unroll(disable)
+                for (int i1 = 0; i1 < 2 * W; ++i1) {
+                    const int c1 = i1 >> 1;
+                    float own = 0.0f, ti = 0.0f, dl1[W], q1 = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < W; ++c) {
+                        own = c == c1 ? x[c] : own;
+                        ti = c == c1 ? ((i1 & 1) ? t[2 * c + 1] : t[2 * c]) : ti;
+                    }
+                    const bool mine = c1 < d && long_step(ti, q, trust);
+                    if (!__any(mine)) continue;
+                    const float h = fd_half_step(pd.fd_h, own);
+                    own = ((i1 & 1) ? own - h : own + h) - s_rec[k * (R / 4) + (T + c1) / 4][(T + c1) % 4];
+#pragma unroll
+                    for (int c = 0; c < W; ++c) dl1[c] = c == c1 ? own : dl[c];
+#pragma unroll
+                    for (int c = 0; c < W; ++c) {
+                        float acc = 0.0f;
+#pragma unroll
+                        for (int j = 0; j < W; ++j) {
+                            const int lo = c < j ? c : j, hi = c < j ? j : c;
+                            acc = fmaf(rec[lo * W - lo * (lo - 1) / 2 + (hi - lo)], dl1[j], acc);
+                        }
+                        q1 = fmaf(dl1[c], acc, q1);
+                    }
+#pragma unroll
+                    for (int c = 0; c < 2 * W; ++c) t[c] = c == i1 && mine ? q1 : t[c];
+                }
+#pragma unroll
+            for (int c = 0; c < 2 * W; ++c) t[c] = component_log2<FAM>(rec[T + W], t[c], nupd, inv_nu);
             st.add(t);
         }
     }
