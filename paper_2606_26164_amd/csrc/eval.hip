@@ -54,6 +54,11 @@ constexpr float kLn2 = 0.6931471805599453f;
 // online log-sum-exp: headroom (log2) a term may exceed the running reference
 // before the reference moves
 constexpr float kLseSlack = 8.0f;
+// The reference a sum starts from.  A part of a split sum that does not begin
+// with component 0 starts from a finite one, so that a component whose term is
+// 2^-inf (its quadratic form overflowed) adds nothing to it, as it does further
+// on in an unsplit sum; from -inf the sum of such a part would be a NaN.
+__device__ __forceinline__ float lse_start(bool at_component_0) { return at_component_0 ? -INFINITY : -__FLT_MAX__; }
 // Student-t kernel in base 2: log2(1 + q / nu) with the hardware log2.
 // Rounding 1 + q / nu costs at most 2^-24 absolute in the argument, i.e.
 // 1.7e-7 in the log, which the factor (nu + d) / 2 scales to a few 1e-6:
@@ -935,11 +940,15 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     for (int ks = 0; ks < KS; ++ks) xB[nb][ks] *= cn[nb];
                 }
             }
+            const int K = __builtin_amdgcn_readfirstlane(pd.K);
+            const int wvu = __builtin_amdgcn_readfirstlane(wv);
+            const int kb = SPLIT == 1 ? 0 : (wvu * K) / SPLIT, ke = SPLIT == 1 ? K : ((wvu + 1) * K) / SPLIT;
+            const float m_start = lse_start(!DSPLIT || kb == 0);
             float mrun[NB], srun[NB];
             float gacc[NB][GRAD ? KS : 1];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                mrun[nb] = -INFINITY;
+                mrun[nb] = m_start;
                 srun[nb] = 0.0f;
                 if constexpr (GRAD)
 #pragma unroll
@@ -1023,7 +1032,7 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
             };
             // contracts one component for the first NBA column blocks of the tile
             // log-sum-exp state of the lane's own block in the two-block path
-            float m_own = -INFINITY, s_own = 0.0f;
+            float m_own = m_start, s_own = 0.0f;
             auto own_to_blocks = [&](auto nba) {
                 if constexpr (decltype(nba)::value == 2) {
                     rows_pair_split(m_own, mrun[0], mrun[1]);
@@ -1187,9 +1196,6 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     }
                 }
             };
-            const int K = __builtin_amdgcn_readfirstlane(pd.K);
-            const int wvu = __builtin_amdgcn_readfirstlane(wv);
-            const int kb = SPLIT == 1 ? 0 : (wvu * K) / SPLIT, ke = SPLIT == 1 ? K : ((wvu + 1) * K) / SPLIT;
             if constexpr (SHARE) {
                 auto loop = [&](auto four) {
                     auto lc = [&](int k) {
@@ -1264,8 +1270,9 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
             if constexpr (DSPLIT) {
                 // merge: m the largest reference, the sums scaled by 2^(m_v - m)
                 // and added in wave order; each wave takes its share of the
-                // coordinates.  A part without components has reference -inf
-                // and sum 0, one that met a NaN has sum NaN.
+                // coordinates.  A part without components, or with none whose
+                // term counts, has its first reference and sum 0; one that
+                // met a NaN has sum NaN.
                 constexpr int NBM = HT ? 1 : NB;
 #pragma unroll
                 for (int nb = 0; nb < NBM; ++nb) {
@@ -1630,7 +1637,7 @@ __global__ __launch_bounds__(kAluBlock) void alu_direct_kernel(EvalArgs a) {
     const float nu = pd.nu, nupd = pd.nu_plus_d, inv_nu = 1.0f / nu;
     const uint32_t i = (SPLIT > 1 ? blockIdx.x : blockIdx.x * kWaves + wv) * kWave + lane;
     const bool in = i < (uint32_t)a.ext_n;
-    float xr[W], ga[GRAD ? W : 1], m = -INFINITY, sm = 0.0f;
+    float xr[W], ga[GRAD ? W : 1], m = lse_start(SPLIT == 1 || wv == 0), sm = 0.0f;
 #pragma unroll
     for (int c = 0; c < W; ++c) {
         xr[c] = (in && c < d) ? as_global(a.X)[(size_t)i * d + c] : 0.0f;
@@ -1807,10 +1814,10 @@ hipError_t launch_alu_direct(const EvalArgs &a, int d, int family, int K, bool g
 template <int NS>
 struct LseStates {
     float m[NS], s[NS];
-    __device__ __forceinline__ void clear() {
+    __device__ __forceinline__ void clear(bool at_component_0) {
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
-            m[i] = -INFINITY;
+            m[i] = lse_start(at_component_0);
             s[i] = 0.0f;
         }
     }
@@ -1912,9 +1919,10 @@ __global__ __launch_bounds__(kWave * kFdWaves) void mixture_fd_kernel(EvalArgs a
     const __amdgpu_buffer_rsrc_t rs_mu = table_rsrc(pd.muB, (uint32_t)K * DP * 4u);
     const __amdgpu_buffer_rsrc_t rs_lc = table_rsrc(pd.logc2, (uint32_t)K * 4u);
     LseStates<2 * KS> st;
-    st.clear();
+    const int k_begin = SPLIT ? (int)((long)K * wv / kFdWaves) : 0;
     const int k_end = SPLIT ? (int)((long)K * (wv + 1) / kFdWaves) : K;
-    for (int k = SPLIT ? (int)((long)K * wv / kFdWaves) : 0; k < k_end; ++k) {
+    st.clear(k_begin == 0);
+    for (int k = k_begin; k < k_end; ++k) {
         const int pf_k = k * DP * DP * 4, mu_k = k * DP * 4;
         float pa[KS][MB], diag[KS], dl[KS];
 #pragma unroll
@@ -2033,7 +2041,7 @@ __global__ __launch_bounds__(kAluBlock) void alu_fd_kernel(EvalArgs a) {
         hm[c] = dn - x[c];
     }
     LseStates<2 * W> st;
-    st.clear();
+    st.clear(!SPLIT || wv == 0);
     for (int k0 = 0; k0 < K; k0 += kAluChunk) {
         const int n = min(kAluChunk, K - k0);
         if (k0) __syncthreads();
