@@ -450,10 +450,13 @@ int direct_split(int DP, int family, int K, long tiles) {
 //
 // SHARE (large two-part launches): four waves take 32 points each of a
 // 128-point tile and go through the components together.  A component's
-// fragments are brought to LDS once for the four, by direct loads one component
-// ahead, instead of through the vector cache four times (16 KB each for
-// about 2000 cycles of work): 262144 points, K = 128, values and gradients 905
-// -> 867 us, values 859 -> 808; a cycle of 65536 samples 20.2 -> 19.0 ms.
+// fragments are brought to LDS once for the four, by direct loads into the half
+// of the buffer that is not being read, instead of through the vector cache
+// four times (16 KB each for about 2000 cycles of work): 262144 points, K =
+// 128, values and gradients 905 -> 867 us, values 859 -> 808; a cycle of 65536
+// samples 20.2 -> 19.0 ms.  (The compiler cannot tell the halves apart and
+// waits for the loads of component k + 1 before it reads component k, so what
+// hides their latency is the other workgroup of the CU, not this one's work.)
 constexpr int kShareWaves = 4;
 template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT, bool H16, bool SHARE = false>
 __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((amdgpu_waves_per_eu(2))) void eval_kernel(EvalArgs a) {
@@ -974,8 +977,8 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
             const __amdgpu_buffer_rsrc_t rs_mu = table_rsrc(H16 ? pd.muB2 : pd.muB, (uint32_t)Kc * DP * 4u);
             const __amdgpu_buffer_rsrc_t rs_lc = table_rsrc(pd.logc2, (uint32_t)Kc * 4u);
             const int mu_lane = g * KS * 4;
-            // (SHARE) component k into half b of s_pts, by every thread; waited
-            // for by the next barrier
+            // (SHARE) component k into half b of s_pts, by every thread; there
+            // after the next arrive()
             [[maybe_unused]] auto fetch = [&](int k, int b) {
                 typedef const void __attribute__((address_space(1))) * gptr;
                 typedef void __attribute__((address_space(3))) * lptr;
@@ -988,6 +991,12 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                 if (threadIdx.x < DP / 4)
                     __builtin_amdgcn_global_load_lds((gptr)(pd.muB2 + (size_t)k * DP + 4 * threadIdx.x),
                                                      (lptr)(dst + DP * DP), 16, 0, 0);
+            };
+            // Direct loads write LDS outside of what a barrier waits for: each
+            // wave waits for its own, then for the others.
+            [[maybe_unused]] auto arrive = [&] {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
             };
             [[maybe_unused]] auto load_shared = [&](int b, Regs &r) {
                 if constexpr (SHARE) {
@@ -1204,7 +1213,7 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     __syncthreads();  // the points are in registers
                     float lc_next = lc(0);
                     fetch(0, 0);
-                    __syncthreads();
+                    arrive();
                     for (int k = 0; k < K; ++k) {
                         ra.lc2 = lc_next;
                         const int kn = min(k + 1, K - 1);
@@ -1212,7 +1221,7 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                         fetch(kn, (k + 1) & 1);
                         load_shared(k & 1, ra);
                         step(ra, AllBlocks{}, four);
-                        __syncthreads();
+                        arrive();
                     }
                 };
                 if (d <= kTwoPartLowD) loop(std::true_type{});
