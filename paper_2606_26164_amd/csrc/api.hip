@@ -336,20 +336,55 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
     {
         hipStream_t st = h->stream;
         HIP_GO(hipGetDevice(&h->device));
-        int *bad;
-        ALLOC(bad, int, 1);
-        HIP_GO(hipMemsetAsync(bad, 0, sizeof(int), st));
+        // ---- component tables in float32, and which problems contract in two
+        // f16 parts: those that two_part_problem accepts and whose matrices
+        // are well-conditioned, which the kernel finds (flags: a matrix that is
+        // not positive definite, then one entry a problem) ----
+        struct Tables {
+            float *Pfrag = nullptr, *muB = nullptr, *logc2 = nullptr, *mu = nullptr, *prec = nullptr;
+        };
+        std::vector<Tables> tab(P);
+        std::vector<std::array<float, 64>> xs(P);
+        std::vector<float> kq(P, 1.0f);
+        std::vector<int> two_part(P), split(P), flags(P + 1);
+        int *flags_dev;
+        ALLOC(flags_dev, int, P + 1);
+        HIP_GO(hipMemsetAsync(flags_dev, 0, sizeof(int) * (P + 1), st));
+        for (int p = 0; p < n_problems; ++p) {
+            const chisao_problem &pr = ps[p];
+            if (pr.family >= CHISAO_RASTRIGIN) continue;  // closed-form functions have no component arrays
+            const size_t d = pr.d, K = pr.K, DP = pad_dim(pr.d, pr.family);
+            Tables &t = tab[p];
+            float *tw;
+            // (in a two-part population read by chisao_eval's differences)
+            ALLOC(t.Pfrag, float, K * DP * DP);
+            ALLOC(t.muB, float, K * DP);
+            ALLOC(t.logc2, float, K);
+            ALLOC(tw, float, K);
+            ALLOC(t.mu, float, K * d);
+            ALLOC(t.prec, float, K * d * d);
+            HIP_GO(hipMemcpyAsync(tw, pr.log_w, sizeof(float) * K, hipMemcpyHostToDevice, st));
+            HIP_GO(hipMemcpyAsync(t.mu, pr.mu, sizeof(float) * K * d, hipMemcpyHostToDevice, st));
+            HIP_GO(hipMemcpyAsync(t.prec, pr.prec, sizeof(float) * K * d * d, hipMemcpyHostToDevice, st));
+            two_part[p] = two_part_problem(pr, xs[p].data(), &kq[p]);
+            HIP_GO(launch_prepare(pr.family, pr.d, (int)DP, pr.K, pr.family == CHISAO_STUDENT_T ? pr.nu : 1.0f, tw,
+                                  t.mu, t.prec, t.logc2, t.Pfrag, t.muB, flags_dev,
+                                  two_part[p] ? flags_dev + 1 + p : nullptr, st));
+        }
+        HIP_GO(hipMemcpyAsync(flags.data(), flags_dev, sizeof(int) * (P + 1), hipMemcpyDeviceToHost, st));
+        HIP_GO(hipStreamSynchronize(st));
+        if (flags[0]) {
+            rc = fail(CHISAO_E_INVAL, "a precision matrix is not positive definite");
+            goto fail_out;
+        }
+        for (int p = 0; p < n_problems; ++p) {
+            two_part[p] = two_part[p] && !flags[1 + p];
+            split[p] = two_part[p] && cs[p].N >= kTwoPartMinN;
+        }
         // ---- per-problem constants ----
         // Samples are laid out problem after problem, ordered by (padded d,
         // family, gradient mode, contraction), so the problems of each launch
         // class own a contiguous range of samples.
-        std::vector<std::array<float, 64>> xs(P);
-        std::vector<float> kq(P, 1.0f);
-        std::vector<int> two_part(P), split(P);
-        for (int p = 0; p < n_problems; ++p) {
-            two_part[p] = two_part_problem(ps[p], xs[p].data(), &kq[p]);
-            split[p] = two_part[p] && cs[p].N >= kTwoPartMinN;
-        }
         std::vector<int> order(P);
         for (int p = 0; p < n_problems; ++p) order[p] = p;
         // Within a class the problems go in decreasing order of K (a tile's
@@ -378,33 +413,19 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             const size_t d = pr.d, K = closed ? 0 : pr.K, DP = pad_dim(pr.d, pr.family);
             ProblemDesc &q = h->pdh[p];
             memset(&q, 0, sizeof q);
-            float *Pfrag = nullptr, *muB = nullptr, *logc2 = nullptr, *lo, *hi;
-            float *Pfrag2 = nullptr, *muB2 = nullptr, *xs_dev = nullptr;
+            const Tables &t = tab[p];
+            float *Pfrag2 = nullptr, *muB2 = nullptr, *xs_dev = nullptr, *lo, *hi;
             ALLOC(lo, float, d);
             ALLOC(hi, float, d);
             HIP_GO(hipMemcpyAsync(lo, pr.lo, sizeof(float) * d, hipMemcpyHostToDevice, st));
             HIP_GO(hipMemcpyAsync(hi, pr.hi, sizeof(float) * d, hipMemcpyHostToDevice, st));
             const float nu = pr.family == CHISAO_STUDENT_T ? pr.nu : 1.0f;
-            if (!closed) {
-                float *tw, *tmu, *tprec;
-                // (in a two-part population read by chisao_eval's differences)
-                ALLOC(Pfrag, float, K * DP * DP);
-                ALLOC(muB, float, K * DP);
-                ALLOC(logc2, float, K);
-                ALLOC(tw, float, K);
-                ALLOC(tmu, float, K * d);
-                ALLOC(tprec, float, K * d * d);
-                HIP_GO(hipMemcpyAsync(tw, pr.log_w, sizeof(float) * K, hipMemcpyHostToDevice, st));
-                HIP_GO(hipMemcpyAsync(tmu, pr.mu, sizeof(float) * K * d, hipMemcpyHostToDevice, st));
-                HIP_GO(hipMemcpyAsync(tprec, pr.prec, sizeof(float) * K * d * d, hipMemcpyHostToDevice, st));
-                if (two_part[p]) {
-                    ALLOC(Pfrag2, float, K * DP * DP);
-                    ALLOC(muB2, float, K * DP);
-                    ALLOC(xs_dev, float, DP);
-                    HIP_GO(hipMemcpyAsync(xs_dev, xs[p].data(), sizeof(float) * DP, hipMemcpyHostToDevice, st));
-                }
-                HIP_GO(launch_prepare(pr.family, pr.d, (int)DP, pr.K, nu, tw, tmu, tprec, logc2, Pfrag, muB, xs_dev,
-                                      kq[p], Pfrag2, muB2, bad, st));
+            if (two_part[p]) {
+                ALLOC(Pfrag2, float, K * DP * DP);
+                ALLOC(muB2, float, K * DP);
+                ALLOC(xs_dev, float, DP);
+                HIP_GO(hipMemcpyAsync(xs_dev, xs[p].data(), sizeof(float) * DP, hipMemcpyHostToDevice, st));
+                HIP_GO(launch_two_part_tables(pr.d, (int)DP, pr.K, t.mu, t.prec, xs_dev, kq[p], Pfrag2, muB2, st));
             }
             q.d = pr.d;
             q.DP = (int)DP;
@@ -412,9 +433,9 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
             q.family = pr.family;
             q.nu = nu;
             q.nu_plus_d = nu + (float)pr.d;
-            q.Pfrag = Pfrag;
-            q.muB = muB;
-            q.logc2 = logc2;
+            q.Pfrag = t.Pfrag;
+            q.muB = t.muB;
+            q.logc2 = t.logc2;
             q.Pfrag2 = Pfrag2;
             q.muB2 = muB2;
             q.xs = xs_dev;
@@ -569,13 +590,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         HIP_GO(hipMemsetAsync(D.ctl, 0, sizeof(Ctl) * P, st));
         HIP_GO(hipMemsetAsync(D.records, 0, sizeof(CycleRecord) * P * D.n_osc, st));
         HIP_GO(hipMemsetAsync(D.prof, 0, sizeof(unsigned long long) * kProfClasses, st));
-        int bad_h = 0;
-        HIP_GO(hipMemcpyAsync(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost, st));
         HIP_GO(hipStreamSynchronize(st));
-        if (bad_h) {
-            rc = fail(CHISAO_E_INVAL, "a precision matrix is not positive definite");
-            goto fail_out;
-        }
         if (x0_dev) {
             // starting populations must lie in their boxes
             for (int p = 0; p < n_problems; ++p) {
@@ -1482,7 +1497,7 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
         used = (used + bytes + 255) & ~(size_t)255;
         return at;
     };
-    const size_t o_pd = take(sizeof(ProblemDesc)), o_cls = take(2 * sizeof(int)), o_ctl = take(sizeof(Ctl));
+    const size_t o_pd = take(sizeof(ProblemDesc)), o_cls = take(3 * sizeof(int)), o_ctl = take(sizeof(Ctl));
     const size_t o_bad = o_cls + sizeof(int), o_xs = take(4 * 64), o_lo = take(4 * d), o_hi = take(4 * d);
     size_t o_pf = 0, o_mub = 0, o_lc = 0, o_w = 0, o_mu = 0, o_prec = 0;
     if (!closed) {
@@ -1512,10 +1527,11 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     q.nu = nu;
     q.nu_plus_d = nu + (float)p->d;
     float xs[64];
-    // one set of tables at a time: the one the values are read from, then (in
-    // the same place) the float32 one of central differences
+    // one set of tables at a time: the float32 one, and where values contract in
+    // two f16 parts that one in its place, then for central differences the
+    // float32 one again
     const bool fd_grad = grad_mode == CHISAO_GRAD_FD && G_dev, values = grad_mode == CHISAO_GRAD_ADJOINT || f_dev;
-    const bool two_part = two_part_problem(*p, xs, &q.kq) && values;
+    bool two_part = two_part_problem(*p, xs, &q.kq) && values;
     float *pf = closed ? nullptr : (float *)(base + o_pf), *mub = closed ? nullptr : (float *)(base + o_mub);
     float *xs_dev = two_part ? (float *)(base + o_xs) : nullptr;
     q.Pfrag = pf;
@@ -1531,35 +1547,38 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     q.noise_sigma = p->noise_sigma;  // recorded only: evaluations on caller memory carry no noise
     Ctl ctl;
     memset(&ctl, 0, sizeof ctl);
-    const int zero = 0;
+    const int zero[2] = {0, 0};
     // every section that must start at zero is written from the host: a fill
     // of the same bytes would also do, this keeps the call to copies only
     HIP_TRY(hipMemcpyAsync(base + o_pd, &q, sizeof q, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + o_cls, &zero, sizeof zero, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(base + o_cls, zero, sizeof(int), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + o_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + o_bad, &zero, sizeof zero, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(base + o_bad, zero, sizeof zero, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + o_lo, p->lo, 4 * d, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + o_hi, p->hi, 4 * d, hipMemcpyHostToDevice, st));
-    auto prepare = [&](bool two) {
-        return launch_prepare(p->family, p->d, (int)DP, p->K, nu, (const float *)(base + o_w),
-                              (const float *)(base + o_mu), (const float *)(base + o_prec), (float *)(base + o_lc),
-                              two ? nullptr : pf, two ? nullptr : mub, two ? xs_dev : nullptr, q.kq, two ? pf : nullptr,
-                              two ? mub : nullptr, (int *)(base + o_bad), st);
+    const float *mu_dev = (const float *)(base + o_mu), *prec_dev = (const float *)(base + o_prec);
+    auto prepare = [&](bool again) {
+        int *flags = (int *)(base + o_bad);
+        return launch_prepare(p->family, p->d, (int)DP, p->K, nu, (const float *)(base + o_w), mu_dev, prec_dev,
+                              again ? nullptr : (float *)(base + o_lc), pf, mub, flags, two_part ? flags + 1 : nullptr,
+                              st);
     };
     if (!closed) {
         HIP_TRY(hipMemcpyAsync(base + o_w, p->log_w, 4 * K, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(base + o_mu, p->mu, 4 * K * d, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(base + o_prec, p->prec, 4 * K * d * d, hipMemcpyHostToDevice, st));
         if (two_part) HIP_TRY(hipMemcpyAsync(xs_dev, xs, 4 * DP, hipMemcpyHostToDevice, st));
-        HIP_TRY(prepare(two_part));
+        HIP_TRY(prepare(false));
     }
     // one synchronization: the host descriptors above stay alive until their
     // copies are done, and a matrix that is not positive definite is reported
     // before anything is evaluated
-    int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, base + o_bad, sizeof bad, hipMemcpyDeviceToHost, st));
+    int flags[2] = {0, 0};
+    HIP_TRY(hipMemcpyAsync(flags, base + o_bad, sizeof flags, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (bad) return fail(CHISAO_E_INVAL, "a precision matrix is not positive definite");
+    if (flags[0]) return fail(CHISAO_E_INVAL, "a precision matrix is not positive definite");
+    two_part = two_part && !flags[1];
+    if (two_part) HIP_TRY(launch_two_part_tables(p->d, (int)DP, p->K, mu_dev, prec_dev, xs_dev, q.kq, pf, mub, st));
     EvalArgs a;
     memset(&a, 0, sizeof a);
     a.D.P = 1;
@@ -1577,7 +1596,7 @@ extern "C" int chisao_eval_static(const chisao_problem *p, float fd_h, const flo
     a.split = two_part;
     if (two_part && fd_grad) {
         HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, (int)K, X_dev, B, f_dev, nullptr, grad_mode, st));
-        HIP_TRY(prepare(false));
+        HIP_TRY(prepare(true));
         f_dev = nullptr;
     }
     HIP_TRY(ext_eval_launches(a, p->d, (int)DP, p->family, (int)K, X_dev, B, f_dev, G_dev, grad_mode, st));

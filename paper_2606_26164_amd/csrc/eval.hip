@@ -135,13 +135,18 @@ struct CompRegs {
 // the rate of the float32 one), summed in float32; up to d = kTwoPartLowD the
 // fourth, l_P l_d, as well.  h and l hold 23 of the 24 significant bits of x, so a term
 // is off by about a rounding of float32, and a sum goes through 3 DP / 32
-// accumulations instead of DP / 4.  Measured against float64 (relative, 2-norm
-// over 4000 points and more, K = 3 to 128, both families): gradients 1.4e-7
-// where the float32 contraction gives 1.7e-7 (d = 64), 1.1e-7 against 1.2e-7
-// (d = 32), 0.93e-7 against 0.95e-7 (d = 20); values alike (6e-8).  Without
-// l_P l_d the d = 20 gradients were at 1.07e-7 and those of d = 33 at 1.26e-7
-// (float32 1.21e-7), and at d = 12 four products gave 9e-8 against 7e-8: so
-// kTwoPartLowD, and DP = 16 stays in float32.
+// accumulations instead of the DP / 4 roundings of the float32 instruction's.
+// Which of the two is further off depends on the matrices; the rule below takes
+// two parts where float32 is.  Errors against float64 (relative, 2-norm, K = 8
+// and 12, spectra log-uniform over a factor c, both families, points of the
+// mixture), two parts over float32, gradients: c = 3: 0.97 (d = 20), 0.77
+// (28), 0.72 (64); c = 10: 1.03, 0.90, 0.84; c = 20: 1.01, 0.92, 0.88; values
+// 0.94 to 1.05.  Outside of the rule: d = 17 1.05 to 1.12; spectra over 10^4
+// 1.3 to 1.5, with one small eigenvalue of 10^-4 values 3.4; matrices that are
+// multiples of the identity 1.9, for there float32 rounds delta and one product
+// (2e-8 against 4e-8).  Without l_P l_d the d = 20 gradients were 15% and those
+// of d = 33 4% further off, and at d = 12 four products gave 9e-8 against
+// 7e-8: so kTwoPartLowD, and DP = 16 stays in float32.
 //
 // What bounds it: the matrix core's rate under load (the products alone ran at
 // 1480 TFLOP/s) plus the vector instructions that split delta (two conversions
@@ -159,11 +164,17 @@ struct CompRegs {
 // What a part holds is then good to 2^-25 absolutely where its own 11 bits do
 // not reach.  The rule below keeps that harmless: problems whose box spans
 // more than 2^kTwoPartSpan of the narrowest component's standard deviations,
-// or whose diagonals differ by more than 2^kTwoPartRatio, stay in float32.  A
+// or whose diagonals differ by more than 2^kTwoPartRatio, stay in float32.  So
+// do, for the errors above, d < kTwoPartMinD; a component fewer than three
+// quarters of whose off-diagonal entries exceed 2^-16 sqrt(P_ii P_jj) (diagonal,
+// banded and block matrices: float32 rounds a sum only where it adds something);
+// and one whose mean P_jj (P^-1)_jj is above two_part_kappa (2.5, 2 below d =
+// 24; the square by which a point's terms exceed their sum; 1.5 for spectra
+// over 10, 1.9 over 20, 4.6 over 100), which prepare_kernel finds.  A
 // point far outside the box carries a power of two of its own (1 for any other
 // point), so nothing overflows that would not in float32.
 // ---------------------------------------------------------------------------
-constexpr int kTwoPartMinD = 17, kTwoPartLowD = 48;
+constexpr int kTwoPartMinD = 20, kTwoPartLowD = 48;
 constexpr int kTwoPartP = 12, kTwoPartX = 13, kTwoPartSpan = 10, kTwoPartRatio = 12, kTwoPartMaxB = 12;
 
 bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, const float *lo, const float *hi,
@@ -188,11 +199,23 @@ bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, c
             if (!(ldexp((double)prec[((size_t)k * d + j) * d + j], -2 * e[j]) >= ldexp(1.0, -kTwoPartRatio)))
                 return false;
     if (!(span <= ldexp(1.0, kTwoPartSpan))) return false;
+    for (int k = 0; k < K; ++k) {
+        const float *P = prec + (size_t)k * d * d;
+        int full = 0;
+        for (int i = 0; i < d; ++i)
+            for (int j = 0; j < i; ++j) {
+                const double v = P[i * d + j];
+                full += v * v >= 0x1p-32 * P[i * d + i] * P[j * d + j];
+            }
+        if (4 * full < 3 * (d * (d - 1) / 2)) return false;
+    }
     const int b = span > 0.0 ? (int)fmin((double)kTwoPartMaxB, kTwoPartX - ceil(log2(span))) : kTwoPartMaxB;
     for (int j = 0; j < DP; ++j) xs[j] = j < d ? (float)ldexp(1.0, e[j] + b) : 1.0f;
     *kq = (float)ldexp(1.0, -2 * b - kTwoPartP);
     return true;
 }
+
+float two_part_kappa(int d) { return d < 24 ? 2.0f : 2.5f; }
 
 // The coordinate a lane of row g holds at position i of its DP / 4: every
 // fourth one, the operand order of the float32 instruction (K = 4).  The f16
@@ -2341,13 +2364,16 @@ hipError_t launch_eval(EvalArgs a, int DP, int family, int center, bool fd, bool
 // Per-component constants.  One workgroup per component: float64 Cholesky of
 // the precision matrix for log|P_k| (setup only), then the MFMA fragment
 // layouts (or, at the VALU width, the component records).  bad[0] is set when
-// a matrix is not positive definite.
+// a matrix is not positive definite; ill[0] (not null) when its mean P_jj
+// (P^-1)_jj exceeds kappa.  logc2 null: the layouts alone.
 // ---------------------------------------------------------------------------
 // Two-part tables of component k: fragments [part][K step][row block][lane]
 // in the f16 instruction's A-operand order, rows permuted as lane_coord
 // states, and the scaled centre in the lanes' order ([row][position]).
-__device__ void two_part_tables(int d, int DP, int k, int lane, const float *A, const float *mu, const float *xs,
-                                float kq, float *Pfrag, float *muB) {
+__global__ __launch_bounds__(64) void two_part_kernel(int d, int DP, const float *mu_all, const float *prec,
+                                                      const float *xs, float kq, float *Pfrag, float *muB) {
+    const int k = blockIdx.x, lane = threadIdx.x;
+    const float *A = prec + (size_t)k * d * d, *mu = mu_all + (size_t)k * d;
     const int KS = DP / 4, MB = DP / 16, S = DP / 32;
     _Float16 *P = reinterpret_cast<_Float16 *>(Pfrag + (size_t)k * DP * DP);
     const int rho = lane & 15;
@@ -2370,53 +2396,73 @@ __device__ void two_part_tables(int d, int DP, int k, int lane, const float *A, 
     }
 }
 
+// Mean over j of P_jj (P^-1)_jj from the Cholesky factor L (lower triangle, row
+// stride d): lane j solves L y = e_j, (P^-1)_jj = |y|^2.
+__device__ float mean_kappa(int d, const float *A, const double *L, int lane) {
+    __shared__ float Y[64][64];
+    double sq = 0.0;
+    for (int i = 0; i < d; ++i) {
+        double acc = i == lane ? 1.0 : 0.0;
+        for (int c = 0; c < i; ++c) acc -= L[i * d + c] * (double)Y[c][lane];
+        const double y = acc / L[i * d + i];
+        Y[i][lane] = (float)y;
+        sq += y * y;
+    }
+    float v = lane < d ? (float)(sq * (double)A[lane * d + lane]) : 0.0f;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
+    return v / (float)d;
+}
+
 __global__ __launch_bounds__(64) void prepare_kernel(int family, int d, int DP, int K, float nu, const float *log_w,
                                                      const float *mu, const float *prec, float *logc2, float *Pfrag,
-                                                     float *muB, const float *xs, float kq, float *Pfrag2,
-                                                     float *muB2, int *bad) {
+                                                     float *muB, int *bad, int *ill, float kappa) {
     const int k = blockIdx.x;
     const int lane = threadIdx.x;
     __shared__ double L[64 * 64];
     __shared__ double diag_log[64];
     const float *A = prec + (size_t)k * d * d;
-    for (int e = lane; e < d * d; e += 64) L[e] = (double)A[e];
-    __syncthreads();
-    // right-looking Cholesky, one column at a time
-    for (int j = 0; j < d; ++j) {
-        if (lane == 0) {
-            double v = L[j * d + j];
-            if (!(v > 0.0)) {
-                atomicExch(bad, 1);
-                v = 1.0;
+    if (logc2) {
+        for (int e = lane; e < d * d; e += 64) L[e] = (double)A[e];
+        __syncthreads();
+        // right-looking Cholesky, one column at a time
+        for (int j = 0; j < d; ++j) {
+            if (lane == 0) {
+                double v = L[j * d + j];
+                if (!(v > 0.0)) {
+                    atomicExch(bad, 1);
+                    v = 1.0;
+                }
+                L[j * d + j] = sqrt(v);
+                diag_log[j] = log(L[j * d + j]);
             }
-            L[j * d + j] = sqrt(v);
-            diag_log[j] = log(L[j * d + j]);
+            __syncthreads();
+            for (int i = j + 1 + lane; i < d; i += 64) L[i * d + j] /= L[j * d + j];
+            __syncthreads();
+            for (int e = lane; e < (d - j - 1) * (d - j - 1); e += 64) {
+                const int i = j + 1 + e / (d - j - 1), c = j + 1 + e % (d - j - 1);
+                if (c <= i) L[i * d + c] -= L[i * d + j] * L[c * d + j];
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        for (int i = j + 1 + lane; i < d; i += 64) L[i * d + j] /= L[j * d + j];
-        __syncthreads();
-        for (int e = lane; e < (d - j - 1) * (d - j - 1); e += 64) {
-            const int i = j + 1 + e / (d - j - 1), c = j + 1 + e % (d - j - 1);
-            if (c <= i) L[i * d + c] -= L[i * d + j] * L[c * d + j];
+        if (lane == 0) {
+            double logdet = 0.0;
+            for (int j = 0; j < d; ++j) logdet += 2.0 * diag_log[j];
+            const double log_2pi = 1.8378770664093454835606594728112;
+            double c;
+            if (family == 0) {
+                c = -0.5 * d * log_2pi + 0.5 * logdet;
+            } else {
+                c = lgamma(0.5 * ((double)nu + d)) - lgamma(0.5 * (double)nu) - 0.5 * d * log((double)nu * M_PI) +
+                    0.5 * logdet;
+            }
+            logc2[k] = (float)(((double)log_w[k] + c) * 1.4426950408889634);
+            if (DP == kAluDP) {
+                const int W = alu_width(d), T = W * (W + 1) / 2;
+                Pfrag[(size_t)k * alu_record(W) + T + W] = logc2[k];
+            }
         }
-        __syncthreads();
-    }
-    if (lane == 0) {
-        double logdet = 0.0;
-        for (int j = 0; j < d; ++j) logdet += 2.0 * diag_log[j];
-        const double log_2pi = 1.8378770664093454835606594728112;
-        double c;
-        if (family == 0) {
-            c = -0.5 * d * log_2pi + 0.5 * logdet;
-        } else {
-            c = lgamma(0.5 * ((double)nu + d)) - lgamma(0.5 * (double)nu) - 0.5 * d * log((double)nu * M_PI) +
-                0.5 * logdet;
-        }
-        logc2[k] = (float)(((double)log_w[k] + c) * 1.4426950408889634);
-        if (DP == kAluDP) {
-            const int W = alu_width(d), T = W * (W + 1) / 2;
-            Pfrag[(size_t)k * alu_record(W) + T + W] = logc2[k];
-        }
+        if (ill && !(mean_kappa(d, A, L, lane) <= kappa) && lane == 0) atomicExch(ill, 1);
     }
     if (DP == kAluDP) {
         // one record per component: upper triangle of P row by row, mu, and
@@ -2436,8 +2482,6 @@ __global__ __launch_bounds__(64) void prepare_kernel(int family, int d, int DP, 
         if (lane > 0 && lane < R - T - W) rec[T + W + lane] = 0.0f;
         return;
     }
-    if (xs) two_part_tables(d, DP, k, lane, A, mu + (size_t)k * d, xs, kq, Pfrag2, muB2);
-    if (!Pfrag) return;
     // fragments with permuted rows: Pfrag[k][ks][lane][mb] = P[pi][4 ks + lane/16],
     // pi = 4 (4 mb + rho % 4) + rho / 4 for rho = lane % 16
     const int KS = DP / 4, MB = DP / 16;
@@ -2457,10 +2501,16 @@ __global__ __launch_bounds__(64) void prepare_kernel(int family, int d, int DP, 
 }
 
 hipError_t launch_prepare(int family, int d, int DP, int K, float nu, const float *log_w, const float *mu,
-                          const float *prec, float *logc2, float *Pfrag, float *muB, const float *xs, float kq,
-                          float *Pfrag2, float *muB2, int *bad, hipStream_t st) {
+                          const float *prec, float *logc2, float *Pfrag, float *muB, int *bad, int *ill,
+                          hipStream_t st) {
     hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(64), 0, st, family, d, DP, K, nu, log_w, mu, prec, logc2, Pfrag,
-                       muB, xs, kq, Pfrag2, muB2, bad);
+                       muB, bad, ill, two_part_kappa(d));
+    return hipGetLastError();
+}
+
+hipError_t launch_two_part_tables(int d, int DP, int K, const float *mu, const float *prec, const float *xs, float kq,
+                                  float *Pfrag2, float *muB2, hipStream_t st) {
+    hipLaunchKernelGGL(two_part_kernel, dim3(K), dim3(64), 0, st, d, DP, mu, prec, xs, kq, Pfrag2, muB2);
     return hipGetLastError();
 }
 

@@ -72,16 +72,22 @@ hipError_t launch_eval(EvalArgs a, int DP, int family, int center, bool fd, bool
 int trial_resident_blocks(int DP, int family, bool split, bool grad);
 
 // Per-component constants: log2 normalisers (float64 Cholesky of each
-// precision matrix) and the fragment layouts of the precision matrices and
-// centres (device buffers): in float32 (Pfrag, muB; null: not wanted) and, xs
-// not null, in two f16 parts (Pfrag2, muB2) with the coordinate scales xs
-// (device, [DP]) and their kq.
+// precision matrix; logc2 null: not again) and the float32 fragment layouts of
+// the precision matrices and centres (device buffers).  *bad is set when a
+// matrix is not positive definite; *ill, where not null, when one is too
+// ill-conditioned for the contraction in two f16 parts.
 hipError_t launch_prepare(int family, int d, int DP, int K, float nu, const float *log_w, const float *mu,
-                          const float *prec, float *logc2, float *Pfrag, float *muB, const float *xs, float kq,
-                          float *Pfrag2, float *muB2, int *bad, hipStream_t st);
+                          const float *prec, float *logc2, float *Pfrag, float *muB, int *bad, int *ill,
+                          hipStream_t st);
 
-// Whether a mixture contracts in two f16 parts, and with which scales
-// (xs [DP], host): the rule and the scales are stated with the definition.
+// The tables of the contraction in two f16 parts, from the scales xs (device,
+// [DP]) and kq of two_part_scales.
+hipError_t launch_two_part_tables(int d, int DP, int K, const float *mu, const float *prec, const float *xs, float kq,
+                                  float *Pfrag2, float *muB2, hipStream_t st);
+
+// Whether a mixture contracts in two f16 parts if none of its matrices is ill
+// (launch_prepare), and with which scales (xs [DP], host): the rule and the
+// scales are stated with the definition.
 bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, const float *lo, const float *hi,
                      float *xs, float *kq);
 
