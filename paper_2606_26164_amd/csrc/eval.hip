@@ -135,18 +135,19 @@ struct CompRegs {
 // the rate of the float32 one), summed in float32; up to d = kTwoPartLowD the
 // fourth, l_P l_d, as well.  h and l hold 23 of the 24 significant bits of x, so a term
 // is off by about a rounding of float32, and a sum goes through 3 DP / 32
-// accumulations instead of the DP / 4 roundings of the float32 instruction's.
+// accumulations; the float32 instruction rounds once a coordinate.
 // Which of the two is further off depends on the matrices; the rule below takes
-// two parts where float32 is.  Errors against float64 (relative, 2-norm, K = 8
-// and 12, spectra log-uniform over a factor c, both families, points of the
-// mixture), two parts over float32, gradients: c = 3: 0.97 (d = 20), 0.77
-// (28), 0.72 (64); c = 10: 1.03, 0.90, 0.84; c = 20: 1.01, 0.92, 0.88; values
-// 0.94 to 1.05.  Outside of the rule: d = 17 1.05 to 1.12; spectra over 10^4
-// 1.3 to 1.5, with one small eigenvalue of 10^-4 values 3.4; matrices that are
-// multiples of the identity 1.9, for there float32 rounds delta and one product
-// (2e-8 against 4e-8).  Without l_P l_d the d = 20 gradients were 15% and those
-// of d = 33 4% further off, and at d = 12 four products gave 9e-8 against
-// 7e-8: so kTwoPartLowD, and DP = 16 stays in float32.
+// two parts where float32 is.  Errors of gradients against float64, two parts
+// over float32 (2-norm over 24 to 300 matrices with log-uniform spectra over a
+// factor 10 and 20, points of their component): d = 20 1.00 and 1.04, 21 1.00
+// and 1.03, 24 0.94 and 0.96, 28 0.89 and 0.92, 32 0.84 and 0.86, 36 0.88 and
+// 0.85, 48 0.77 and 0.75, 49 0.96 and 0.98, 64 0.84 and 0.85; values 0.94 to
+// 1.05.  Outside of the rule: d = 19 1.02 and 1.06, 17 1.05 to 1.12; spectra
+// over 10^4 1.3 to 1.5, with one small eigenvalue of 10^-4 values 3.4; multiples
+// of the identity 1.9, for there float32 rounds delta and one product (2e-8
+// against 4e-8).  Without l_P l_d the gradients of d = 33 were 4% further off,
+// and at d = 12 four products gave 9e-8 against 7e-8: so kTwoPartLowD, and DP =
+// 16 stays in float32.
 //
 // What bounds it: the matrix core's rate under load (the products alone ran at
 // 1480 TFLOP/s) plus the vector instructions that split delta (two conversions
@@ -168,13 +169,14 @@ struct CompRegs {
 // do, for the errors above, d < kTwoPartMinD; a component fewer than three
 // quarters of whose off-diagonal entries exceed 2^-16 sqrt(P_ii P_jj) (diagonal,
 // banded and block matrices: float32 rounds a sum only where it adds something);
-// and one whose mean P_jj (P^-1)_jj is above two_part_kappa (2.5, 2 below d =
-// 24; the square by which a point's terms exceed their sum; 1.5 for spectra
-// over 10, 1.9 over 20, 4.6 over 100), which prepare_kernel finds.  A
+// and one whose mean P_jj (P^-1)_jj is above two_part_kappa (the square by which
+// a point's terms exceed their sum; up to 1.8 for spectra over 10, 2.4 over 20,
+// 4.6 in the mean over 100), which prepare_kernel finds.  A
 // point far outside the box carries a power of two of its own (1 for any other
 // point), so nothing overflows that would not in float32.
 // ---------------------------------------------------------------------------
 constexpr int kTwoPartMinD = 20, kTwoPartLowD = 48;
+constexpr float two_part_kappa(int d) { return d < 24 ? 1.9f : 2.5f; }
 constexpr int kTwoPartP = 12, kTwoPartX = 13, kTwoPartSpan = 10, kTwoPartRatio = 12, kTwoPartMaxB = 12;
 
 bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, const float *lo, const float *hi,
@@ -214,8 +216,6 @@ bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, c
     *kq = (float)ldexp(1.0, -2 * b - kTwoPartP);
     return true;
 }
-
-float two_part_kappa(int d) { return d < 24 ? 2.0f : 2.5f; }
 
 // The coordinate a lane of row g holds at position i of its DP / 4: every
 // fourth one, the operand order of the float32 instruction (K = 4).  The f16
@@ -1087,34 +1087,54 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                 // the same coordinates 4 ks + g, so delta also serves the
                 // quadratic form below
                 float bv[NB][KS];
-                if constexpr (H16) {
-#pragma unroll
-                    for (int s = 0; s < r.S; ++s) {
-                        f16x8 bh[NB], bl[NB];
-#pragma unroll
-                        for (int nb = 0; nb < NBA; ++nb) {
-#pragma unroll
-                            for (int j = 0; j < 8; ++j)
-                                bv[nb][8 * s + j] = fmaf(-r.muB[8 * s + j], cn[nb], xB[nb][8 * s + j]);
-                            two_parts(&bv[nb][8 * s], neg1, bh[nb], bl[nb]);
-                        }
-                        // the small products first, while the accumulator is
-                        // small; consecutive instructions go to different
-                        // accumulators
+                // (two parts) acc += P v for the blocks b0 .. b1 - 1; fill(s, v) gives
+                // the deltas of K step s.  The small products go first, while the
+                // accumulator is small: all of them where the second step holds
+                // few coordinates (d <= kTwoPartLowD of 64; step by step those of
+                // d = 36 were 1.03 times float32's error off), else, to save
+                // registers, those of a step before its large one.
+                [[maybe_unused]] auto contract = [&](const Regs &r, auto &&fill, auto b0, auto b1) {
+                    if constexpr (H16) {
+                        constexpr bool LATE = FOUR && Regs::S > 1;
+                        f16x8 bh[LATE ? Regs::S : 1][NB], bl[NB];
+                        // consecutive instructions go to different accumulators
                         auto product = [&](const f16x8(&pa)[MB], const f16x8(&b)[NB]) {
 #pragma unroll
                             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                                for (int nb = 0; nb < NBA; ++nb)
+                                for (int nb = b0.value; nb < b1.value; ++nb)
                                     acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa[mb], b[nb], acc[nb][mb], 0, 0, 0);
                         };
-                        __builtin_amdgcn_s_setprio(1);
-                        if constexpr (FOUR) product(r.pa[1][s], bl);
-                        product(r.pa[0][s], bl);
-                        product(r.pa[1][s], bh);
-                        product(r.pa[0][s], bh);
-                        __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+                        for (int s = 0; s < Regs::S; ++s) {
+                            const int o = LATE ? s : 0;
+                            float v[NB][8];
+                            fill(s, v);
+#pragma unroll
+                            for (int nb = b0.value; nb < b1.value; ++nb) two_parts(v[nb], neg1, bh[o][nb], bl[nb]);
+                            __builtin_amdgcn_s_setprio(1);
+                            if constexpr (FOUR) product(r.pa[1][s], bl);
+                            product(r.pa[0][s], bl);
+                            product(r.pa[1][s], bh[o]);
+                            if constexpr (!LATE) product(r.pa[0][s], bh[o]);
+                            __builtin_amdgcn_s_setprio(0);
+                        }
+                        if constexpr (LATE) {
+                            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                            for (int s = 0; s < Regs::S; ++s) product(r.pa[0][s], bh[s]);
+                            __builtin_amdgcn_s_setprio(0);
+                        }
                     }
+                };
+                if constexpr (H16) {
+                    contract(r, [&](int s, float(&v)[NB][8]) {
+#pragma unroll
+                        for (int nb = 0; nb < NBA; ++nb)
+#pragma unroll
+                            for (int j = 0; j < 8; ++j)
+                                v[nb][j] = bv[nb][8 * s + j] = fmaf(-r.muB[8 * s + j], cn[nb], xB[nb][8 * s + j]);
+                    }, std::integral_constant<int, 0>{}, nba);
                 } else {
                 __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -1136,16 +1156,21 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     // rows 1 and 3 block 1's (the same arithmetic as the
                     // per-block path below, half the lanes' work each), and
                     // the gradient weights are exchanged back to every lane.
-                    float q0 = 0.0f, q1 = 0.0f;
+                    auto form = [&] {
+                        float q0 = 0.0f, q1 = 0.0f;
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
+                        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) {
-                            q0 = fmaf(bv[0][4 * mb + rr], acc[0][mb][rr], q0);
-                            q1 = fmaf(bv[1][4 * mb + rr], acc[1][mb][rr], q1);
-                        }
-                    float q = rows4_sum_pair(q0, q1);
-                    if constexpr (H16) q *= kq_own;
+                            for (int rr = 0; rr < 4; ++rr) {
+                                q0 = fmaf(bv[0][4 * mb + rr], acc[0][mb][rr], q0);
+                                q1 = fmaf(bv[1][4 * mb + rr], acc[1][mb][rr], q1);
+                            }
+                        return rows4_sum_pair(q0, q1);
+                    };
+                    float q = form();
+                    if constexpr (H16) {
+                        q *= kq_own;
+                    }
                     float l2, w = 1.0f;
                     if constexpr (FAM == 0) {
                         l2 = r.lc2 - q * (0.5f * kLog2e);
@@ -1189,13 +1214,18 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                 }
 #pragma unroll
                 for (int nb = 0; nb < NBA; ++nb) {
-                    float q = 0.0f;
+                    auto form = [&] {
+                        float q = 0.0f;
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
+                        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) q = fmaf(bv[nb][4 * mb + rr], acc[nb][mb][rr], q);
-                    q = rows4_sum(q);
-                    if constexpr (H16) q *= kqn[nb];
+                            for (int rr = 0; rr < 4; ++rr) q = fmaf(bv[nb][4 * mb + rr], acc[nb][mb][rr], q);
+                        return rows4_sum(q);
+                    };
+                    float q = form();
+                    if constexpr (H16) {
+                        q *= kqn[nb];
+                    }
                     float l2, w = 1.0f;
                     if constexpr (FAM == 0) {
                         l2 = r.lc2 - q * (0.5f * kLog2e);

@@ -11,7 +11,7 @@ from test_gpu_eval import _opt
 
 pytestmark = pytest.mark.gpu
 
-ROWS, PROBLEMS = 300, 8
+ROWS = 300
 
 
 def _matrix(rng, d, kind, c):
@@ -41,15 +41,12 @@ def _chain(P, D):
     return acc.astype(np.float64)
 
 
-@pytest.mark.parametrize("kind,c", [("log", 1), ("log", 3), ("log", 10), ("log", 100), ("log", 1e4), ("one", 100),
-                                    ("one", 1e4), ("banded", 0), ("blocks", 0), ("weak", 0)])
-@pytest.mark.parametrize("d", [17, 20, 24, 33, 49, 64])
-def test_gradients_are_as_good_as_a_float32_contraction(d, kind, c):
-    """One component, so that a gradient is -P delta; 6% for the scatter between
-    8 problems' worth of matrices (each matrix's own rounding is a fixed error)."""
+def _ratio(d, kind, c, problems):
+    """Error of the library's gradients over that of the chain, both against
+    float64.  One component, so that a gradient is -P delta."""
     rng = np.random.default_rng(d)
     got, ref = 0.0, 0.0
-    for i in range(PROBLEMS):
+    for _ in range(problems):
         P = _matrix(rng, d, kind, c).astype(np.float32)
         mu = rng.uniform(-5.0, 5.0, (1, d)).astype(np.float32)
         prob = W.Problem(W.GAUSS, d, 1, np.zeros(1, np.float32), mu, P[None], np.full(d, -6.0, np.float32),
@@ -62,4 +59,18 @@ def test_gradients_are_as_good_as_a_float32_contraction(d, kind, c):
         scale = np.linalg.norm(exact)
         got += (np.linalg.norm(G - exact) / scale) ** 2
         ref += (np.linalg.norm(-_chain(P, X - mu) - exact) / scale) ** 2
-    assert got <= 1.06 ** 2 * ref, f"{np.sqrt(got / ref):.3f} times the error of a float32 contraction"
+    return np.sqrt(got / ref)
+
+
+@pytest.mark.parametrize("kind,c", [("log", 1), ("log", 3), ("log", 10), ("log", 100), ("log", 1e4), ("one", 100),
+                                    ("one", 1e4), ("banded", 0), ("blocks", 0), ("weak", 0)])
+@pytest.mark.parametrize("d", [17, 20, 24, 33, 49, 64])
+def test_gradients_are_as_good_as_a_float32_contraction(d, kind, c):
+    """6% for the scatter between 8 matrices' worth (a matrix's own rounding is
+    a fixed error)."""
+    assert _ratio(d, kind, c, 8) <= 1.06
+
+
+@pytest.mark.parametrize("d", [24, 32, 33, 36, 40, 48, 52, 64])
+def test_no_further_off_over_many_matrices(d):
+    assert _ratio(d, "log", 10, 32) <= 1.0 + 1e-6  # (float32 itself where the rule takes it: the same sums)
