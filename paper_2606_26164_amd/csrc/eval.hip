@@ -171,7 +171,11 @@ struct CompRegs {
 // banded and block matrices: float32 rounds a sum only where it adds something);
 // and one whose mean P_jj (P^-1)_jj is above two_part_kappa (the square by which
 // a point's terms exceed their sum; up to 1.8 for spectra over 10, 2.4 over 20,
-// 4.6 in the mean over 100), which prepare_kernel finds.  A
+// 4.6 in the mean over 100), which prepare_kernel finds.
+// Next to a centre at or near 0 float32 holds every digit of a small delta, and
+// 2^-25 is too much: a point within 4 2^-b standard deviations of a centre is
+// contracted again with that component, its delta scaled up (a few evaluations
+// at the end of an ascent; a branch that other waves skip).  A
 // point far outside the box carries a power of two of its own (1 for any other
 // point), so nothing overflows that would not in float32.
 // ---------------------------------------------------------------------------
@@ -1062,6 +1066,11 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                 }
                 r.lc2 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs_lc, 0, k * 4, 0));
             };
+            // k, as a value the compiler does not know to be k
+            [[maybe_unused]] auto hidden = [](int k) {
+                asm("" : "+s"(k));
+                return k;
+            };
             // contracts one component for the first NBA column blocks of the tile
             // log-sum-exp state of the lane's own block in the two-block path
             float m_own = m_start, s_own = 0.0f;
@@ -1074,7 +1083,13 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
             // (two-part problems) the lane's own block's factor of the quadratic form
             float kq_own = 1.0f;
             if constexpr (H16) kq_own = (g & 1) ? kqn[1] : kqn[0];
-            auto step = [&](const Regs &r, auto nba, auto four) {
+            // forms of points that lie within 4 2^-b standard deviations of a
+            // centre (kq = 2^(-2 b - kTwoPartP)): where f16's smallest numbers begin
+            // to show in their deltas
+            [[maybe_unused]] const float q_near = H16 ? pd.kq * (float)(16 << kTwoPartP) : 0.0f;
+            // (two parts) again: the fragments once more, for the rare use far from the
+            // first (held, they would cost 32 registers)
+            auto step = [&](const Regs &r, auto nba, auto four, auto &&again) {
                 constexpr bool FOUR = decltype(four)::value;
                 constexpr int NBA = decltype(nba)::value;
                 f32x4 acc[NB][MB];
@@ -1127,6 +1142,27 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                         }
                     }
                 };
+                // (two parts) u again for the points of block nb that lie next to
+                // the centre, from deltas scaled so that the largest fills f16's
+                // range; the other points' come out as they were
+                [[maybe_unused]] auto contract_near = [&](const Regs &r2, auto b, bool near) {
+                    if constexpr (H16) {
+                        constexpr int nb = decltype(b)::value;
+                        float mx = 0.0f;
+#pragma unroll
+                        for (int ks = 0; ks < KS; ++ks) mx = fmaxf(mx, fabsf(bv[nb][ks]));
+                        const int e = 140 - (int)(__float_as_uint(rows4_max(mx)) >> 23);
+                        const int ex = near ? max(0, min(e, 120)) : 0;
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        contract(r2, [&](int s, float(&v)[NB][8]) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) v[nb][j] = ldexpf(bv[nb][8 * s + j], ex);
+                        }, b, std::integral_constant<int, nb + 1>{});
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] *= ldexpf(1.0f, -ex);
+                    }
+                };
                 if constexpr (H16) {
                     contract(r, [&](int s, float(&v)[NB][8]) {
 #pragma unroll
@@ -1170,6 +1206,15 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     float q = form();
                     if constexpr (H16) {
                         q *= kq_own;
+                        if (__any(q < q_near)) {
+                            float n0, n1;
+                            rows_pair_split(q < q_near ? 1.0f : 0.0f, n0, n1);
+                            Regs r2;
+                            again(r2);
+                            contract_near(r2, std::integral_constant<int, 0>{}, n0 != 0.0f);
+                            contract_near(r2, std::integral_constant<int, 1>{}, n1 != 0.0f);
+                            q = form() * kq_own;
+                        }
                     }
                     float l2, w = 1.0f;
                     if constexpr (FAM == 0) {
@@ -1225,6 +1270,12 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     float q = form();
                     if constexpr (H16) {
                         q *= kqn[nb];
+                        if (__any(q < q_near)) {
+                            Regs r2;
+                            again(r2);
+                            contract_near(r2, std::integral_constant<int, 0>{}, q < q_near);  // (one block only)
+                            q = form() * kqn[nb];
+                        }
                     }
                     float l2, w = 1.0f;
                     if constexpr (FAM == 0) {
@@ -1273,7 +1324,7 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                         lc_next = lc(kn);
                         fetch(kn, (k + 1) & 1);
                         load_shared(k & 1, ra);
-                        step(ra, AllBlocks{}, four);
+                        step(ra, AllBlocks{}, four, [&](Regs &r2) { load_shared(hidden(k) & 1, r2); });
                         arrive();
                     }
                 };
@@ -1292,10 +1343,10 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                         load(kb, ra);
                         for (int k = kb; k < ke; k += 2) {
                             load(min(k + 1, ke - 1), rb);
-                            step(ra, nba, std::true_type{});
+                            step(ra, nba, std::true_type{}, [&](Regs &r2) { load(hidden(k), r2); });
                             if (k + 1 >= ke) break;
                             load(min(k + 2, ke - 1), ra);
-                            step(rb, nba, std::true_type{});
+                            step(rb, nba, std::true_type{}, [&](Regs &r2) { load(hidden(k + 1), r2); });
                         }
                     }
                     own_to_blocks(nba);
@@ -1312,7 +1363,7 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                 auto loop = [&](auto nba, auto four) {
                     for (int k = kb; k < ke; ++k) {
                         load(k, ra);
-                        step(ra, nba, four);
+                        step(ra, nba, four, [&](Regs &r2) { load(hidden(k), r2); });
                     }
                 };
                 auto run = [&](auto nba) {
