@@ -319,7 +319,8 @@ const char *chisao_last_error(void);
 /* Evaluation launch schedules chosen at init.  Problems are grouped into
  * classes by (padded d, family, gradient mode, contraction: float32 products or
  * two f16 parts per operand with float32 sums, the latter for mixtures of d >=
- * 17 with more than 2048 samples whose box and precisions suit it); for each class the autotuner
+ * 24 with more than 2048 samples whose box and precision matrices keep it as
+ * accurate as float32); for each class the autotuner
  * times CHISAO_TUNE_VARIANTS schedules over the starting population, on a
  * value + adjoint gradient pass (adjoint classes) or a central-difference
  * stencil pass (finite-difference classes): each variant once untimed, then

@@ -219,6 +219,9 @@ static int validate_problem(const chisao_problem *p, int idx) {
 // 5.8 ms in float32 and would take 3.4 in two parts; at N = 4096 it is 6.6
 // against 3.8, at N = 65536 42.1 against 19.1.
 constexpr int kTwoPartMinN = 2049;
+// Populations below d = 24 stay in float32 at any size: their gradients at the
+// end of an ascent were 6% further off in two parts (d = 20).
+constexpr int kTwoPartMinPopulationD = 24;
 
 // Two-part contraction of a matrix-core mixture: the scales, when it qualifies.
 static int two_part_problem(const chisao_problem &p, float *xs, float *kq) {
@@ -379,7 +382,7 @@ extern "C" int chisao_init_batched(chisao_handle *out, int n_problems, const chi
         }
         for (int p = 0; p < n_problems; ++p) {
             two_part[p] = two_part[p] && !flags[1 + p];
-            split[p] = two_part[p] && cs[p].N >= kTwoPartMinN;
+            split[p] = two_part[p] && cs[p].N >= kTwoPartMinN && ps[p].d >= kTwoPartMinPopulationD;
         }
         // ---- per-problem constants ----
         // Samples are laid out problem after problem, ordered by (padded d,

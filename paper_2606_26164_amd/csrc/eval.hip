@@ -141,13 +141,17 @@ struct CompRegs {
 // over float32 (2-norm over 24 to 300 matrices with log-uniform spectra over a
 // factor 10 and 20, points of their component): d = 20 1.00 and 1.04, 21 1.00
 // and 1.03, 24 0.94 and 0.96, 28 0.89 and 0.92, 32 0.84 and 0.86, 36 0.88 and
-// 0.85, 48 0.77 and 0.75, 49 0.96 and 0.98, 64 0.84 and 0.85; values 0.94 to
-// 1.05.  Outside of the rule: d = 19 1.02 and 1.06, 17 1.05 to 1.12; spectra
-// over 10^4 1.3 to 1.5, with one small eigenvalue of 10^-4 values 3.4; multiples
-// of the identity 1.9, for there float32 rounds delta and one product (2e-8
-// against 4e-8).  Without l_P l_d the gradients of d = 33 were 4% further off,
-// and at d = 12 four products gave 9e-8 against 7e-8: so kTwoPartLowD, and DP =
-// 16 stays in float32.
+// 0.85, 48 0.77 and 0.75, 53 0.92 and 0.95, 64 0.84 and 0.85; values 0.94 to
+// 1.05.  Next to the end of an ascent, where delta lies along P's small
+// eigenvalues (P^-1 z, z normal): d = 20 1.06 and 1.06, 24 0.97 and 1.02, 28
+// 0.94 and 0.97, 32 0.86 and 0.93, 36 0.91 and 0.86, 48 0.81 and 0.79, 64 0.89
+// and 0.92, so that populations take it from d = 24 on only.  Outside of the
+// rule: d = 19 1.02 and 1.06, 17 1.05 to 1.12; spectra over 10^4 1.3 to 1.5,
+// with one small eigenvalue of 10^-4 values 3.4; multiples of the identity 1.9,
+// for there float32 rounds delta and one product (2e-8 against 4e-8).  Without
+// l_P l_d the gradients of d = 49 were 0.96 and 0.98, at the end of an ascent
+// 1.01 and 1.03, and at d = 12 four products gave 9e-8 against 7e-8: so
+// kTwoPartLowD, and DP = 16 stays in float32.
 //
 // What bounds it: the matrix core's rate under load (the products alone ran at
 // 1480 TFLOP/s) plus the vector instructions that split delta (two conversions
@@ -179,7 +183,7 @@ struct CompRegs {
 // point far outside the box carries a power of two of its own (1 for any other
 // point), so nothing overflows that would not in float32.
 // ---------------------------------------------------------------------------
-constexpr int kTwoPartMinD = 20, kTwoPartLowD = 48;
+constexpr int kTwoPartMinD = 20, kTwoPartLowD = 52;
 constexpr float two_part_kappa(int d) { return d < 24 ? 1.9f : 2.5f; }
 constexpr int kTwoPartP = 12, kTwoPartX = 13, kTwoPartSpan = 10, kTwoPartRatio = 12, kTwoPartMaxB = 12;
 
