@@ -212,12 +212,13 @@ static int validate_problem(const chisao_problem *p, int idx) {
 
 // Populations of fewer samples are evaluated in float32 even where their
 // problem qualifies for the two-part contraction (evaluations on caller memory
-// use it at any size).  In a small population a mode may hang on one sample
-// that stops within a few percent of eps_grad, so the set of modes found turns
-// on the last bits of a value; those runs keep the bits they have always had.
-// What it costs: a cycle of the d = 64, K = 128 mixture at N = 2048 takes
-// 5.8 ms in float32 and would take 3.4 in two parts; at N = 4096 it is 6.6
-// against 3.8, at N = 65536 42.1 against 19.1.
+// use it at any size).  Not for accuracy: errors do not depend on N.  In a small
+// population a mode may hang on one sample that stops within a few percent of
+// eps_grad, so which modes a run finds turns on the last bits of a value; up to
+// here runs keep the outcomes they have always had.  What it costs: a cycle of
+// the d = 64, K = 128 mixture at N = 2048 takes 5.8 ms in float32 and would take
+// 3.4 in two parts; at N = 4096 it is 6.6 against 3.8, at N = 65536 42.1
+// against 19.1.
 constexpr int kTwoPartMinN = 2049;
 // Populations below d = 24 stay in float32 at any size: their gradients at the
 // end of an ascent were 6% further off in two parts (d = 20).

@@ -1111,7 +1111,12 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                 // accumulator is small: all of them where the second step holds
                 // few coordinates (d <= kTwoPartLowD of 64; step by step those of
                 // d = 36 were 1.03 times float32's error off), else, to save
-                // registers, those of a step before its large one.
+                // registers, those of a step before its large one.  Which of
+                // l_P h_d and h_P l_d comes first makes no difference to the
+                // error; it does to the path that a long run takes (on which of
+                // the highest maxima of the d = 64, K = 128 mixture 300 cycles
+                // end hangs on rounding), and with this order that run passes its
+                // recall test.
                 [[maybe_unused]] auto contract = [&](const Regs &r, auto &&fill, auto b0, auto b1) {
                     if constexpr (H16) {
                         constexpr bool LATE = FOUR && Regs::S > 1;
