@@ -327,7 +327,8 @@ const char *chisao_last_error(void);
  * two rounds over the variants, a variant's time its fastest launch (variants
  * whose launches are the same are timed as one).  It
  * keeps the default (variant 0) unless another is at least 3% faster than the
- * best so far: variant v uses
+ * best so far (a closed form's central differences are one launch whatever the
+ * schedule, so such a class keeps the default): variant v uses
  * tile order v % 2 (0 linear, 1 XCD-chunked) and a grid of 8192 (v < 2) or
  * 1024 workgroups.  Then, for an adjoint mixture class on the matrix cores,
  * it times the value + gradient pass in tiles of 16 and of 32 points under

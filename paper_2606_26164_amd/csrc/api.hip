@@ -772,9 +772,10 @@ static int autotune(chisao_ctx *h) {
     hipError_t e = ev.create();
     if (e != hipSuccess) return fail(CHISAO_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
     // a launch of no more tiles than the smallest grid is the same under every
-    // grid size: variants 2 and 3 repeat 0 and 1
-    auto same_as = [](long tiles) {
-        return [tiles](int v) { return v >= 2 && tiles <= kTuneCap[v] ? v - 2 : v; };
+    // grid size: variants 2 and 3 repeat 0 and 1.  (one: the launch takes neither
+    // order nor grid, every variant repeats 0)
+    auto same_as = [](long tiles, bool one = false) {
+        return [tiles, one](int v) { return one ? 0 : (v >= 2 && tiles <= kTuneCap[v] ? v - 2 : v); };
     };
     auto each = [](int v) { return v; };
     for (EvalClass &c : h->eclasses) {
@@ -791,7 +792,7 @@ static int autotune(chisao_ctx *h) {
             a.order = kTuneOrder[v];
             a.grid_cap = kTuneCap[v];
             return launch_eval(a, c.DP, c.family, kDirect, fd, adj, h->stream);
-        }, same_as(a.max_tiles), c.tune_ms);
+        }, same_as(a.max_tiles, fd && c.family >= kFamClosed), c.tune_ms);
         if (e != hipSuccess) break;
         const int best_v = pick_variant(c.tune_ms, kTuneVariants);
         c.order = kTuneOrder[best_v];
