@@ -159,7 +159,8 @@ typedef struct {
     int32_t ls_fail;    /* line searches that failed during Phase 1 */
     int32_t n_nonfinite;/* samples taken out of use at Phase 2 because their value, gate value or gradient
                            was not finite (they join no reduction, are never stuck and are not reseeded) */
-    int64_t evals;      /* objective evaluations (points) during the cycle */
+    int64_t evals;      /* objective evaluations (points) during the cycle; line-search trials as the stages t = 1,
+                           then 1/2 and 1/4, then the rest need them, also where one launch computes them together */
 } chisao_cycle_stats;
 
 /* Host view of the population state for chisao_get_state / chisao_set_state.
@@ -194,7 +195,8 @@ typedef struct {
 /* Kernel timing of the work enqueued by chisao_cycle / chisao_run_phases
  * while profiling is on: HIP events recorded around each launch on the
  * handle's stream, and the number of objective evaluations (points) each
- * evaluation launch processed, counted on the device. */
+ * evaluation launch computed, counted on the device.  The launches are those of
+ * an unprofiled run, in order on one stream. */
 #define CHISAO_PROF_EVAL_DIRECT 0 /* value and adjoint gradient at the samples */
 #define CHISAO_PROF_EVAL_TRIAL 1  /* line-search trial points */
 #define CHISAO_PROF_EVAL_PROBE 2  /* Hands Like Clouds smoothing probes */

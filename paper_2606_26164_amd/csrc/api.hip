@@ -890,8 +890,7 @@ static int in_place_max(int DP) { return DP == kAluDP ? 16384 : (DP == 16 ? 2048
 static hipError_t converge_iteration(chisao_ctx *h, const EvalClass &c, hipStream_t st, int t) {
     const Dev &D = h->D;
     const bool adj = c.grad_mode == CHISAO_GRAD_ADJOINT;
-    // (profiles tally the steppers in the compactions)
-    const bool in_place = c.n <= in_place_max(c.DP) && !h->prof;
+    const bool in_place = c.n <= in_place_max(c.DP);
     hipError_t e;
     // the steppers of iteration t go to list_out; t+1 reads them back
     const int list_in = t == 1 || in_place ? L_ACT : ((t - 1) % 2 ? L_T1 : L_T1B);
@@ -907,10 +906,15 @@ static hipError_t converge_iteration(chisao_ctx *h, const EvalClass &c, hipStrea
          })) != hipSuccess)
         return e;
     if (t > c.nconv) return hipSuccess;
-    // (the L-BFGS step and history-pair tallies are kept only when profiling)
-    if ((e = compact(list_in, list_out, -1, false, h->prof ? D.prof + CHISAO_PROF_LBFGS : nullptr,
-                     h->prof ? D.prof + CHISAO_PROF_LBFGS_PAIRS : nullptr)) != hipSuccess)
-        return e;
+    // (the L-BFGS step and history-pair tallies are kept only when profiling;
+    // in place by a compaction that appends to no list)
+    if (in_place && h->prof)
+        e = launch_compact(D, list_in, -1, -1, false, D.prof + CHISAO_PROF_LBFGS, st, D.prof + CHISAO_PROF_LBFGS_PAIRS,
+                           c.g0, c.n);
+    else
+        e = compact(list_in, list_out, -1, false, h->prof ? D.prof + CHISAO_PROF_LBFGS : nullptr,
+                    h->prof ? D.prof + CHISAO_PROF_LBFGS_PAIRS : nullptr);
+    if (e != hipSuccess) return e;
     // first trial t = 1 for every stepper, then the remaining trials in two
     // stages: t = 1/2, 1/4, then the rest only for searches that rejected
     // those too.  Most searches that reject t = 1 accept one of the next two,

@@ -1555,7 +1555,8 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     if constexpr (GRAD) D.G[o] = s_g[pa * LD + c];
                 }
             }
-            // (evaluation counts of all trials at once are those of two stages)
+            // (a cycle's evaluation count is that of two stages; a profile's
+            // points are those computed)
             if constexpr (FLAGS) {
                 if (lead && a.trial_need > 0 && Vc > a.trial_need) {
                     const bool early = lane < jpw && s_s[lane * Vc] >= 0 && s_acc[lane] >= 0 && s_acc[lane] < a.trial_need;
@@ -1563,7 +1564,6 @@ __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((
                     if (lane == 0 && n) {
                         const unsigned long long not_needed = (unsigned long long)n * (Vc - a.trial_need);
                         atomicAdd(&D.ctl[p].evals, 0ull - not_needed);
-                        atomicAdd(&D.prof[CENTER], 0ull - not_needed);
                     }
                 }
             }
