@@ -281,7 +281,12 @@ int chisao_run_phases(chisao_handle h, uint32_t phase_mask);
  * the method would use): X_dev device [B*d]; f_dev device [B] (may be NULL);
  * G_dev device [B*d] (may be NULL).  grad_mode selects the adjoint kernel or
  * central differences (fd_h of the handle's config).  Enqueued on the
- * handle's stream; does not synchronize. */
+ * handle's stream; does not synchronize.
+ * A row's results do not depend on the other rows, nor on its place among them.
+ * Their last bits may depend on B: with few rows several waves share a
+ * mixture's components, and their sums are added in another order (at B = 4096,
+ * 16384 and 32768 for d > 8, 65536 for d <= 8, as K allows); either way the
+ * value is off by float32 rounding only. */
 int chisao_eval(chisao_handle h, int problem, const float *X_dev, int B, float *f_dev, float *G_dev,
                 int grad_mode);
 

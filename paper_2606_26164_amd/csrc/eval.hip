@@ -209,15 +209,21 @@ bool two_part_scales(int d, int DP, int K, const float *mu, const float *prec, c
             if (!(ldexp((double)prec[((size_t)k * d + j) * d + j], -2 * e[j]) >= ldexp(1.0, -kTwoPartRatio)))
                 return false;
     if (!(span <= ldexp(1.0, kTwoPartSpan))) return false;
+    // (in units of the 2^e_j, where float32 does not overflow)
+    float unit[64], diag[64];
+    for (int j = 0; j < d; ++j) unit[j] = (float)ldexp(1.0, -e[j]);
     for (int k = 0; k < K; ++k) {
         const float *P = prec + (size_t)k * d * d;
-        int full = 0;
-        for (int i = 0; i < d; ++i)
-            for (int j = 0; j < i; ++j) {
-                const double v = P[i * d + j];
-                full += v * v >= 0x1p-32 * P[i * d + i] * P[j * d + j];
+        int full = -d;  // the diagonal's own
+        for (int j = 0; j < d; ++j) diag[j] = 0x1p-32f * (P[j * d + j] * unit[j] * unit[j]);
+        for (int i = 0; i < d; ++i) {
+            const float ui = unit[i], di = 0x1p32f * diag[i];
+            for (int j = 0; j < d; ++j) {
+                const float v = P[i * d + j] * ui * unit[j];
+                full += v * v >= di * diag[j];
             }
-        if (4 * full < 3 * (d * (d - 1) / 2)) return false;
+        }
+        if (4 * full < 3 * d * (d - 1)) return false;
     }
     const int b = span > 0.0 ? (int)fmin((double)kTwoPartMaxB, kTwoPartX - ceil(log2(span))) : kTwoPartMaxB;
     for (int j = 0; j < DP; ++j) xs[j] = j < d ? (float)ldexp(1.0, e[j] + b) : 1.0f;
@@ -488,6 +494,12 @@ int direct_split(int DP, int family, int K, long tiles) {
 // samples 20.2 -> 19.0 ms.  (The compiler cannot tell the halves apart and
 // waits for the loads of component k + 1 before it reads component k, so what
 // hides their latency is the other workgroup of the CU, not this one's work.)
+//
+// Registers: two waves per SIMD leave 256 a lane.  In two parts at width 64 the
+// line-search kernel with gradients keeps 11 more (Gaussian) or 12 (Student-t)
+// in scratch, the direct one whose four waves share a tile 3 or 7, the
+// Student-t probe kernel 3: written once a tile, at most one read back a
+// component beside its 48 matrix instructions.  The float32 forms need none.
 constexpr int kShareWaves = 4;
 template <int DP, int FAM, bool GRAD, int CENTER, bool FD, int SPLIT, bool HT, bool H16, bool SHARE = false>
 __global__ __launch_bounds__(64 * (SHARE ? kShareWaves : SPLIT)) __attribute__((amdgpu_waves_per_eu(2))) void eval_kernel(EvalArgs a) {
@@ -2492,9 +2504,14 @@ __device__ float mean_kappa(int d, const float *A, const double *L, int lane) {
     __shared__ float Y[64][64];
     double sq = 0.0;
     for (int i = 0; i < d; ++i) {
-        double acc = i == lane ? 1.0 : 0.0;
-        for (int c = 0; c < i; ++c) acc -= L[i * d + c] * (double)Y[c][lane];
-        const double y = acc / L[i * d + i];
+        // (four chains, so that the reads of one do not wait for the others)
+        double acc[4] = {i == lane ? 1.0 : 0.0, 0.0, 0.0, 0.0};
+        int c = 0;
+        for (; c + 4 <= i; c += 4)
+#pragma unroll
+            for (int o = 0; o < 4; ++o) acc[o] -= L[i * d + c + o] * (double)Y[c + o][lane];
+        for (; c < i; ++c) acc[0] -= L[i * d + c] * (double)Y[c][lane];
+        const double y = ((acc[0] + acc[1]) + (acc[2] + acc[3])) / L[i * d + i];
         Y[i][lane] = (float)y;
         sq += y * y;
     }
