@@ -53,12 +53,12 @@ def executed_width(d: int) -> int:
 
 def two_part_products(prob, cfg) -> int:
     """f16 matrix products per component of a population's contraction: 0 where
-    it runs in float32 (d <= 16, closed forms, or no more than 2048 samples),
-    else 3, and 4 up to d = 48 (every mixture here meets the rule on the box's
-    span).  The operands are two f16 parts each; the sums are float32."""
-    if prob.family > 1 or prob.d < 17 or cfg.N < 2049:
+    it runs in float32 (d < 24, closed forms, or no more than 2048 samples),
+    else 3, and 4 up to d = 52 (every mixture here meets the rule on the box's
+    span and the matrices' condition).  The operands are two f16 parts each; the sums are float32."""
+    if prob.family > 1 or prob.d < 24 or cfg.N < 2049:
         return 0
-    return 4 if prob.d <= 48 else 3
+    return 4 if prob.d <= 52 else 3
 
 
 def matrix_seconds_per_point(prob, cfg) -> float:
